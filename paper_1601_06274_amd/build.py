@@ -22,19 +22,21 @@ LIB = os.path.join(HERE, "libdmatch.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 # (source, extra defines, object name)
-def _tiles():
-    """The tile list of csrc/tiles.h (one compilation unit per tile)."""
+def _tiles(macro):
+    """A tile list of csrc/tiles.h (one compilation unit per tile)."""
     with open(os.path.join(CSRC, "tiles.h")) as f:
-        return [(int(g), int(l)) for g, l in re.findall(r"X\((\d+),\s*(\d+)\)", f.read())]
+        return [(int(g), int(l)) for g, l in re.findall(macro + r"\((\d+),\s*(\d+)\)", f.read())]
 
 
-TILES = _tiles()
+TILES = _tiles("X")
+PIPE_TILES = _tiles("Y")
 UNITS = [("api.hip", [], "api"), ("dmm.hip", [], "dmm"), ("cost_volume.hip", [], "cost_volume"),
          ("refine.hip", [], "refine"), ("batched.hip", [], "batched"), ("noalloc.hip", [], "noalloc"), ("batched_grad.hip", [], "batched_grad"),
          ("flow.hip", [], "flow")]
 # largest units first so the parallel build's critical path starts early
 UNITS = [("dmm_tile.hip", [f"-DDM_TILE_G={g}", f"-DDM_TILE_L={l}", f"-DDM_TILE_PART={k}"], f"dmm_tile_{g}x{l}_{v}")
          for k, v in [(2, "adj"), (4, "tape"), (1, "fwd"), (3, "batch")] for g, l in sorted(TILES, key=lambda t: -t[0] * t[1])] + UNITS
+UNITS += [("dmm_pipe.hip", [f"-DDM_PIPE_G={g}", f"-DDM_PIPE_L={l}"], f"dmm_pipe_{g}x{l}") for g, l in reversed(PIPE_TILES)]
 # the hierarchical-minorant kernels, one unit per labels-per-lane count (the slowest
 # compiles: first), and their dispatch
 UNITS = ([("dmm_hier.hip", [f"-DDM_HIER_LPL={l}"], f"dmm_hier_{l}") for l in (3, 4, 2, 1)] + UNITS +

@@ -10,6 +10,7 @@
 #include <tuple>
 
 #include "dmm_adjoint.h"
+#include "dmm_pipe.h"
 #include "dmm_hier.h"
 #include "tiles.h"
 
@@ -21,6 +22,9 @@ namespace dm {
     extern template hipError_t launch_adjoint_tile<g, l, true>(const AdjArgs&, dm_dtype, hipStream_t);
 DM_FOR_EACH_TILE(DM_EXTERN_TILE)
 #undef DM_EXTERN_TILE
+#define DM_EXTERN_PIPE(g, l) extern template hipError_t launch_pipe<g, l>(const SweepArgs&, dm_dtype, hipStream_t);
+DM_FOR_EACH_PIPE(DM_EXTERN_PIPE)
+#undef DM_EXTERN_PIPE
 
 // ------------------------------------------------------------------ small kernels
 __global__ void fill_f32_kernel(float* __restrict__ p, long long n, float v) {
@@ -222,12 +226,34 @@ Tile col_tile(const dm_shape& s, const dm_discrete_params& p) {
     return p.tile_lanes_v != 0 ? Tile{p.tile_lanes_v, p.labels_per_lane_v} : row_tile(s, p);
 }
 
-hipError_t launch_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st) {
+hipError_t launch_tile_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st) {
 #define DM_TILE_CASE(g, l) \
     if (t.G == g && t.LPL == l) return launch_tile<g, l>(a, dt, st);
     DM_FOR_EACH_TILE(DM_TILE_CASE)
 #undef DM_TILE_CASE
     return hipErrorInvalidValue;
+}
+
+// The pipelined sweep's tile for a launch, {0, 0} where the one-wave tile kernel is used.
+// The two give the same results bit for bit where the tile's message is the direct window
+// (T <= 3 and its reach within one lane); the scans of larger T round by tile.  The line lies
+// at one workgroup per slot of the chip (by LDS): beyond it a second round of workgroups costs
+// as much again, while the one-wave kernel is at HBM bandwidth (1242 columns of K = 192: 826 us
+// against about 2 x 600).
+Tile pipe_tile(Tile t, const SweepArgs& a) {
+    if ((a.mode & kRecordFlag) != 0 || a.T > 3 || a.T - 1 > t.LPL) return Tile{0, 0};
+    const Tile d = a.K <= 16 ? Tile{16, 1} : (a.K <= 32 ? Tile{32, 1} : Tile{64, (a.K + 63) / 64});
+    const int blocks = (a.n_chains + 64 / d.G - 1) / (64 / d.G);
+    return blocks <= pipe_resident(d.LPL, a.theta != nullptr) ? d : Tile{0, 0};
+}
+
+hipError_t launch_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st) {
+    const Tile d = pipe_tile(t, a);
+#define DM_PIPE_CASE(g, l) \
+    if (d.G == g && d.LPL == l) return launch_pipe<g, l>(a, dt, st);
+    DM_FOR_EACH_PIPE(DM_PIPE_CASE)
+#undef DM_PIPE_CASE
+    return launch_tile_sweep(t, a, dt, st);
 }
 
 hipError_t launch_adjoint(Tile t, const AdjArgs& a, dm_dtype dt, hipStream_t st) {
@@ -1041,11 +1067,11 @@ extern "C" int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_pa
         float best_ms = 1e30f;
         for (const Tile& t : kTiles) {
             if (t.G * t.LPL < s.K) continue;
-            if (launch_sweep(t, a, cost_dtype, stream) != hipSuccess) continue;  // warm-up
+            if (launch_tile_sweep(t, a, cost_dtype, stream) != hipSuccess) continue;  // warm-up
             float ms_min = 1e30f;
             for (int rep = 0; rep < 3; ++rep) {
                 (void)hipEventRecord(e0, stream);
-                (void)launch_sweep(t, a, cost_dtype, stream);
+                (void)launch_tile_sweep(t, a, cost_dtype, stream);
                 (void)hipEventRecord(e1, stream);
                 if (hipEventSynchronize(e1) != hipSuccess) break;
                 float ms = 0.0f;

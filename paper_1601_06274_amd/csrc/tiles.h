@@ -15,3 +15,12 @@
     X(32, 6)                \
     X(64, 3)                \
     X(64, 4)
+
+// Tiles of the pipelined sweeps (dmm_pipe.h), chosen by the library alone.
+#define DM_FOR_EACH_PIPE(Y) \
+    Y(16, 1)               \
+    Y(32, 1)               \
+    Y(64, 1)               \
+    Y(64, 2)               \
+    Y(64, 3)               \
+    Y(64, 4)
