@@ -35,9 +35,12 @@ int check_hip(const char* where);
 
 int validate_shape(const dm_shape& s);
 
-// Contrast edge weights w = lambda_pw * exp(-|I(neighbour) - I| / contrast_sigma) of one
-// image (cost_volume.hip); w_h / w_v may be null.
-hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float contrast_sigma, float* w_h,
+// Contrast edge weights w = lambda_pw * exp(-|I(neighbour) - I| * inv_sigma) of one image
+// (cost_volume.hip); w_h / w_v may be null.
+__device__ __forceinline__ float contrast_weight(float neighbour, float c, float lambda_pw, float inv_sigma) {
+    return lambda_pw * expf(-fabsf(neighbour - c) * inv_sigma);
+}
+hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float inv_sigma, float* w_h,
                                    float* w_v, hipStream_t stream);
 int validate_discrete(const dm_shape& s, const dm_discrete_params* p);
 

@@ -6,68 +6,15 @@
 // (Sec. 3.1); this kernel provides a truncated windowed SAD in the same role.
 // Edge strengths are image dependent, lower across image edges (Sec. 2.1).
 //
-// Layout: the volume is label-major ([y][x][d], d fastest).  A block owns one image row
-// and TX consecutive pixels; its threads are the labels (blockDim = K rounded up to a
-// wave), so each pixel's K costs are one contiguous, coalesced write.  The window rows of
-// both images are staged in LDS; each thread first sums the window vertically for the
-// TX + 2R window columns of its label (registers), then slides the horizontal sum.
-// Border handling: window positions are clamped to the image (clamp-to-edge), and a
-// right-image column left of 0 costs `trunc`.
+// Layout: the volume is label-major ([y][x][d], d fastest).  Windows up to 7 are computed
+// on strips of rows (sad_strip.h).  Border handling: window positions are clamped to the
+// image (clamp-to-edge), and a right-image column left of 0 costs `trunc`.
 #include "common.h"
+#include "sad_strip.h"
 
 namespace dm {
 
-constexpr int kSadTX = 16;  // pixels per block
-
-template <typename OT, int R>
-__global__ __launch_bounds__(256) void sad_tile_kernel(const float* __restrict__ IL, const float* __restrict__ IR, int W,
-                                                       int H, int K, float trunc, float inv_area,
-                                                       OT* __restrict__ out) {
-    constexpr int TX = kSadTX;
-    constexpr int NR = 2 * R + 1;   // window rows
-    constexpr int NC = TX + 2 * R;  // window columns of the tile
-    __shared__ float sL[NR][NC];
-    __shared__ float sR[NR][NC + 255];
-    const int y = blockIdx.y;
-    const int x0 = blockIdx.x * TX;
-    const int lr = x0 - R;            // image column of sL[.][0]
-    const int rr = x0 - R - (K - 1);  // image column of sR[.][0]
-    const int nrc = NC + K - 1;
-    for (int e = threadIdx.x; e < NR * nrc; e += blockDim.x) {
-        const int row = e / nrc, j = e - row * nrc;
-        const int yy = min(max(y + row - R, 0), H - 1);
-        const int xc = rr + j;
-        sR[row][j] = (xc >= 0 && xc < W) ? IR[(long long)yy * W + xc] : 0.0f;
-        if (j < NC) sL[row][j] = IL[(long long)yy * W + min(max(lr + j, 0), W - 1)];
-    }
-    __syncthreads();
-    const int d = threadIdx.x;
-    if (d >= K) return;
-    // vertical window sums at the (clamped) columns lr + i
-    float col[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) {
-        const int xx = min(max(lr + i, 0), W - 1);  // clamped image column
-        const int li = xx - lr;                     // its index in sL
-        const int xr = xx - d;                      // matching right-image column
-        const int ri = xr - rr;
-        float acc = 0.0f;
-#pragma unroll
-        for (int row = 0; row < NR; ++row) acc += (xr >= 0) ? fabsf(sL[row][li] - sR[row][ri]) : trunc;
-        col[i] = acc;
-    }
-#pragma unroll
-    for (int xi = 0; xi < TX; ++xi) {
-        const int x = x0 + xi;
-        if (x >= W) break;
-        float acc = 0.0f;
-#pragma unroll
-        for (int dx = 0; dx < NR; ++dx) acc += col[xi + dx];
-        out[((long long)y * W + x) * K + d] = (OT)fminf(trunc, acc * inv_area);
-    }
-}
-
-// Any odd window (the tiled kernel covers radii 1..3): one thread per (pixel, label).
+// Any odd window (the strips cover radii 0..3): one thread per (pixel, label).
 template <typename OT>
 __global__ __launch_bounds__(256) void sad_kernel(const float* __restrict__ IL, const float* __restrict__ IR, int W,
                                                   int H, int K, int r, float trunc, float inv_area,
@@ -99,17 +46,17 @@ __global__ __launch_bounds__(256) void contrast_kernel(const float* __restrict__
          p += (long long)gridDim.x * blockDim.x) {
         const int x = (int)(p % W), y = (int)(p / W);
         const float c = IL[p];
-        if (w_h != nullptr && x + 1 < W) w_h[(long long)y * (W - 1) + x] = lambda_pw * expf(-fabsf(IL[p + 1] - c) * inv_sigma);
-        if (w_v != nullptr && y + 1 < H) w_v[p] = lambda_pw * expf(-fabsf(IL[p + W] - c) * inv_sigma);
+        if (w_h != nullptr && x + 1 < W)
+            w_h[(long long)y * (W - 1) + x] = contrast_weight(IL[p + 1], c, lambda_pw, inv_sigma);
+        if (w_v != nullptr && y + 1 < H) w_v[p] = contrast_weight(IL[p + W], c, lambda_pw, inv_sigma);
     }
 }
 
-hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float contrast_sigma, float* w_h,
+hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float inv_sigma, float* w_h,
                                    float* w_v, hipStream_t stream) {
     const long long npx = (long long)W * H;
     const unsigned b2 = (unsigned)std::min<long long>((npx + 255) / 256, 65535LL);
-    hipLaunchKernelGGL(contrast_kernel, dim3(b2), dim3(256), 0, stream, I, W, H, lambda_pw, 1.0f / contrast_sigma, w_h,
-                       w_v);
+    hipLaunchKernelGGL(contrast_kernel, dim3(b2), dim3(256), 0, stream, I, W, H, lambda_pw, inv_sigma, w_h, w_v);
     return hipGetLastError();
 }
 
@@ -122,102 +69,118 @@ hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw
 // the image costs `trunc`.  Left view: pixel x matches x - d of the right image; right
 // view: pixel x of the right image matches x + d of the left image.
 //
-// A block owns one image row and TX consecutive pixels; each thread owns a pair of
-// labels (d, d + 1).  The window rows of the reference image (TX codes) and of the
-// matched image (TX + K - 1 codes) are staged in LDS and every code is computed once per
-// block; then each thread writes its two labels' costs for the TX pixels: per label one
-// xor, two popcounts and a table lookup (the table holds min(trunc, h / n) for h = 0..n,
-// each an IEEE division, so every value is the correctly rounded quotient).  PACK (K
-// even): the pair is one 2-element store (its element offset is even, so it is aligned).
-constexpr int kCensusTX = 64;
+// What bounds it: the store of the volume, then the codes.  A block owns one image row and
+// kCensusX pixels: the window rows of the reference image (kCensusX codes) and of the
+// matched image (kCensusX + K - 1 codes) are staged in LDS and every code is computed once
+// per block (in 32 bits for windows up to 5).  Then a thread owns LPT consecutive labels of
+// kCensusTX pixels: the codes of the matched image that its labels and pixels meet are read
+// once into registers, each output is an xor, a bit count and a look-up in a table of
+// min(trunc, h / n), h = 0..n (each an IEEE division, so every value is the correctly rounded
+// quotient; n + 1 words in as many LDS banks), and a pixel's LPT costs are one vector store.
+// The block also writes the contrast weights of its pixels' edges.
+//
+// Measured, 1242 x 375 x 192 FP16, window 5, one view with the weights: see kCensusX.
+constexpr int kCensusX = 128, kCensusTX = 8;
 
-template <typename OT, int R, bool LEFT, bool PACK>
-__global__ __launch_bounds__(128) void census_tile_kernel(const float* __restrict__ IL, const float* __restrict__ IR,
-                                                          int W, int H, int K, float trunc, OT* __restrict__ out) {
-    constexpr int TX = kCensusTX;
-    constexpr int NR = 2 * R + 1;
-    constexpr int NA = TX + 2 * R;  // staged columns of the reference image
-    __shared__ float sA[NR][NA];
-    __shared__ float sB[NR][TX + 255 + 2 * R];
-    __shared__ uint64_t cA[TX];
-    __shared__ uint64_t cB[TX + 255];
+template <int R>
+struct CensusCode {
+    using type = uint32_t;  // (2R+1)^2 - 1 = 8 or 24 bits
+};
+template <>
+struct CensusCode<3> {
+    using type = uint64_t;  // 48 bits
+};
+__device__ __forceinline__ int census_distance(uint32_t a, uint32_t b) { return __popc(a ^ b); }
+__device__ __forceinline__ int census_distance(uint64_t a, uint64_t b) { return __popcll(a ^ b); }
+
+// Code of the pixel at column c + R of the staged rows.
+template <int R, int NC>
+__device__ __forceinline__ typename CensusCode<R>::type census_code(const float (&rows)[2 * R + 1][NC], int c) {
+    using code_t = typename CensusCode<R>::type;
+    const float ctr = rows[R][c + R];
+    code_t v = 0;
+    int b = 0;
+#pragma unroll
+    for (int dy = 0; dy < 2 * R + 1; ++dy)
+#pragma unroll
+        for (int dx = 0; dx < 2 * R + 1; ++dx) {
+            if (dy == R && dx == R) continue;
+            v |= (code_t)(rows[dy][c + dx] < ctr) << b;
+            ++b;
+        }
+    return v;
+}
+
+template <typename OT, int R, bool LEFT, int LPT>
+__global__ __launch_bounds__(256) void census_tile_kernel(const float* __restrict__ IL, const float* __restrict__ IR,
+                                                          int W, int H, int K, float trunc, OT* __restrict__ out,
+                                                          StripWeights sw) {
+    constexpr int TX = kCensusTX, NR = 2 * R + 1, n = NR * NR - 1;
+    using code_t = typename CensusCode<R>::type;
+    __shared__ float sA[NR][kCensusX + 2 * R];
+    __shared__ float sB[NR][kCensusX + 255 + 2 * R];
+    __shared__ code_t cA[kCensusX];
+    __shared__ code_t cB[kCensusX + 255 + 2 * (LPT - 1)];  // codes from LPT - 1 on; padded for labels beyond K
     __shared__ float lut[64];
     const float* __restrict__ A = LEFT ? IL : IR;  // reference image of the view
     const float* __restrict__ B = LEFT ? IR : IL;  // matched image
     const int y = blockIdx.y;
-    const int x0 = blockIdx.x * TX;
-    const int nb = TX + K - 1;                // codes of the matched image
-    const int bA = x0;                         // image column of code cA[0]
-    const int bB = LEFT ? x0 - (K - 1) : x0;  // image column of code cB[0]
-    const int nbs = nb + 2 * R;
+    const int x0 = blockIdx.x * kCensusX;
+    const int nb = kCensusX + K - 1;          // codes of the matched image
+    const int bB = LEFT ? x0 - (K - 1) : x0;  // image column of the first
 #pragma unroll
     for (int row = 0; row < NR; ++row) {
         const long long yy = min(max(y + row - R, 0), H - 1);
         const float* __restrict__ Brow = B + yy * W;
-        for (int j = threadIdx.x; j < nbs; j += blockDim.x) sB[row][j] = Brow[min(max(bB - R + j, 0), W - 1)];
+        for (int j = threadIdx.x; j < nb + 2 * R; j += blockDim.x) sB[row][j] = Brow[min(max(bB - R + j, 0), W - 1)];
         const float* __restrict__ Arow = A + yy * W;
-        for (int j = threadIdx.x; j < NA; j += blockDim.x) sA[row][j] = Arow[min(max(bA - R + j, 0), W - 1)];
+        for (int j = threadIdx.x; j < kCensusX + 2 * R; j += blockDim.x)
+            sA[row][j] = Arow[min(max(x0 - R + j, 0), W - 1)];
     }
-    constexpr int n = NR * NR - 1;
     if (threadIdx.x <= n) lut[threadIdx.x] = fminf(trunc, (float)threadIdx.x / (float)n);
     __syncthreads();
-    // codes: staged column c's window is columns c .. c + 2R of the staged rows
-    for (int c = threadIdx.x; c < TX + nb; c += blockDim.x) {
-        const bool isA = c < TX;
-        const int cc = isA ? c : c - TX;
-        uint64_t v = 0;
-        int b = 0;
-        if (isA) {
-            const float ctr = sA[R][cc + R];
-#pragma unroll
-            for (int dy = 0; dy < NR; ++dy)
-#pragma unroll
-                for (int dx = 0; dx < NR; ++dx) {
-                    if (dy == R && dx == R) continue;
-                    v |= (uint64_t)(sA[dy][cc + dx] < ctr) << b;
-                    ++b;
-                }
-            cA[cc] = v;
-        } else {
-            const float ctr = sB[R][cc + R];
-#pragma unroll
-            for (int dy = 0; dy < NR; ++dy)
-#pragma unroll
-                for (int dx = 0; dx < NR; ++dx) {
-                    if (dy == R && dx == R) continue;
-                    v |= (uint64_t)(sB[dy][cc + dx] < ctr) << b;
-                    ++b;
-                }
-            cB[cc] = v;
-        }
+    for (int c = threadIdx.x; c < kCensusX; c += blockDim.x) {
+        cA[c] = census_code<R>(sA, c);
+        const int x = x0 + c;
+        if (sw.w_h != nullptr && x + 1 < W)
+            sw.w_h[(long long)y * (W - 1) + x] = contrast_weight(sA[R][c + R + 1], sA[R][c + R], sw.lambda_pw, sw.inv_sigma);
+        if (sw.w_v != nullptr && x < W && y + 1 < H)
+            sw.w_v[(long long)y * W + x] = contrast_weight(sA[R + 1][c + R], sA[R][c + R], sw.lambda_pw, sw.inv_sigma);
     }
+    for (int c = threadIdx.x; c < nb; c += blockDim.x) cB[LPT - 1 + c] = census_code<R>(sB, c);
     __syncthreads();
-    const int d0 = 2 * (int)threadIdx.x;
-    if (d0 >= K) return;
-    const bool two = d0 + 1 < K;  // always with PACK
-    const int nx = min(TX, W - x0);
-    const float tr = trunc;
-    auto cost = [&](int xi, int d) -> float {
-        const int x = x0 + xi;
-        const int xo = LEFT ? x - d : x + d;            // matched column
-        const int jb = LEFT ? xi + K - 1 - d : xi + d;  // its code index
-        return (xo >= 0 && xo < W) ? lut[__popcll(cA[xi] ^ cB[jb])] : tr;
-    };
-    OT* __restrict__ o = out + ((long long)y * W + x0) * K + d0;
-#pragma unroll 8
-    for (int xi = 0; xi < nx; ++xi) {
-        const float c0 = cost(xi, d0);
-        if constexpr (PACK) {
-            typedef OT pair_t __attribute__((ext_vector_type(2)));
-            pair_t v;
-            v.x = (OT)c0;
-            v.y = (OT)cost(xi, d0 + 1);
-            *reinterpret_cast<pair_t*>(o) = v;
-        } else {
-            o[0] = (OT)c0;
-            if (two) o[1] = (OT)cost(xi, d0 + 1);
+    const int groups = (K + LPT - 1) / LPT;
+    const bool interior = bB >= 0 && bB + nb <= W && x0 + kCensusX <= W;
+    for (int item = threadIdx.x; item < (kCensusX / TX) * groups; item += blockDim.x) {
+        const int g = item / groups;
+        const int i0 = (item - g * groups) * LPT;
+        const int xa = x0 + g * TX;
+        if (xa >= W) continue;
+        // pixel q and label i0 + l meet code vb[q + LPT - 1 - l] (left) or vb[q + l] (right)
+        const code_t* b = cB + g * TX + (LEFT ? K - 1 - i0 : i0 + LPT - 1);
+        code_t va[TX], vb[TX + LPT - 1];
+#pragma unroll
+        for (int q = 0; q < TX; ++q) va[q] = cA[g * TX + q];
+#pragma unroll
+        for (int q = 0; q < TX + LPT - 1; ++q) vb[q] = b[q];
+        OT* o = out + ((long long)y * W + xa) * K + i0;
+#pragma unroll
+        for (int q = 0; q < TX; ++q) {
+            if (xa + q < W) {
+                typedef OT vec_t __attribute__((ext_vector_type(LPT)));
+                vec_t r;
+#pragma unroll
+                for (int l = 0; l < LPT; ++l) {
+                    float c = lut[census_distance(va[q], vb[LEFT ? q + LPT - 1 - l : q + l])];
+                    if (!interior) {
+                        const int xo = LEFT ? xa + q - (i0 + l) : xa + q + (i0 + l);  // matched column
+                        c = (xo >= 0 && xo < W) ? c : trunc;
+                    }
+                    r[l] = (OT)c;
+                }
+                *reinterpret_cast<vec_t*>(o + (long long)q * K) = r;
+            }
         }
-        o += K;
     }
 }
 
@@ -276,21 +239,28 @@ extern "C" int dm_build_cost_volume_census(const float* I_left, const float* I_r
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     const long long total = (long long)s.W * s.H * s.K;
     ProfScope ps(DM_PROF_CENSUS, (double)total * (out_dtype == DM_F16 ? 2 : 4) + 8.0 * s.W * s.H, stream);
-    const dim3 grid((unsigned)((s.W + kCensusTX - 1) / kCensusTX), (unsigned)s.H);
-    const dim3 block((unsigned)(((s.K + 1) / 2 + 63) / 64 * 64));  // one thread per label pair
+    const dim3 grid((unsigned)((s.W + kCensusX - 1) / kCensusX), (unsigned)s.H);
     const bool left = view == DM_VIEW_LEFT;
-    const bool pack = (s.K % 2) == 0;
-#define DM_CENSUS_V(OT, RR, LF, PK)                                                                                 \
-    hipLaunchKernelGGL((census_tile_kernel<OT, RR, LF, PK>), grid, block, 0, stream, I_left, I_right, s.W, s.H, s.K, \
-                       p->trunc, static_cast<OT*>(cost_out))
+    const StripWeights sw{w_h, w_v, p->lambda_pw, 1.0f / p->contrast_sigma};
+    const size_t es = out_dtype == DM_F16 ? 2 : 4;
+    // the widest vector that K and the volume's alignment allow; the items spread evenly
+    const int lpt = (s.K % 4 == 0 && (uintptr_t)cost_out % (4 * es) == 0) ? 4
+                    : (s.K % 2 == 0 && (uintptr_t)cost_out % (2 * es) == 0) ? 2 : 1;
+    const int items = (kCensusX / kCensusTX) * ((s.K + lpt - 1) / lpt), turns = (items + 255) / 256;
+    const dim3 block((unsigned)(((items + turns - 1) / turns + 63) / 64 * 64));
+#define DM_CENSUS_V(OT, RR, LF, LP)                                                                                 \
+    hipLaunchKernelGGL((census_tile_kernel<OT, RR, LF, LP>), grid, block, 0, stream, I_left, I_right, s.W, s.H, s.K, \
+                       p->trunc, static_cast<OT*>(cost_out), sw)
 #define DM_CENSUS(OT, RR)                                     \
     do {                                                      \
         if (left) {                                           \
-            if (pack) DM_CENSUS_V(OT, RR, true, true);        \
-            else DM_CENSUS_V(OT, RR, true, false);            \
+            if (lpt == 4) DM_CENSUS_V(OT, RR, true, 4);       \
+            else if (lpt == 2) DM_CENSUS_V(OT, RR, true, 2);  \
+            else DM_CENSUS_V(OT, RR, true, 1);                \
         } else {                                              \
-            if (pack) DM_CENSUS_V(OT, RR, false, true);       \
-            else DM_CENSUS_V(OT, RR, false, false);           \
+            if (lpt == 4) DM_CENSUS_V(OT, RR, false, 4);      \
+            else if (lpt == 2) DM_CENSUS_V(OT, RR, false, 2); \
+            else DM_CENSUS_V(OT, RR, false, 1);               \
         }                                                     \
     } while (0)
     const int r = p->window / 2;
@@ -307,13 +277,6 @@ extern "C" int dm_build_cost_volume_census(const float* I_left, const float* I_r
 #undef DM_CENSUS_V
     ps.stop();
     DM_HIP_TRY(hipGetLastError(), "census launch");
-    if (w_h != nullptr || w_v != nullptr) {
-        const long long npx = (long long)s.W * s.H;
-        const unsigned b2 = (unsigned)std::min<long long>((npx + 255) / 256, 65535LL);
-        hipLaunchKernelGGL(contrast_kernel, dim3(b2), dim3(256), 0, stream, left ? I_left : I_right, s.W, s.H,
-                           p->lambda_pw, 1.0f / p->contrast_sigma, w_h, w_v);
-        DM_HIP_TRY(hipGetLastError(), "contrast launch");
-    }
     return DM_OK;
 }
 
@@ -371,35 +334,34 @@ extern "C" int dm_build_cost_volume(const float* I_left, const float* I_right, d
     const float inv_area = 1.0f / (float)(p->window * p->window);
     // algorithmic bytes: the volume written once, the two images read once
     ProfScope ps(DM_PROF_COST_VOLUME, (double)total * (out_dtype == DM_F16 ? 2 : 4) + 8.0 * s.W * s.H, stream);
-    const dim3 tgrid((unsigned)((s.W + kSadTX - 1) / kSadTX), (unsigned)s.H);
-    const dim3 tblock((unsigned)((s.K + 63) / 64 * 64));
-#define DM_SAD_TILE(OT, RR) \
-    hipLaunchKernelGGL((sad_tile_kernel<OT, RR>), tgrid, tblock, 0, stream, I_left, I_right, s.W, s.H, s.K, p->trunc, \
-                       inv_area, static_cast<OT*>(cost_out))
+    hipError_t strip = hipSuccess;
+    const StripWeights sw{w_h, w_v, p->lambda_pw, 1.0f / p->contrast_sigma};
+#define DM_SAD_STRIP(OT, RR)                                                                                        \
+    strip = launch_sad_strip<OT, RR, -1>(I_left, I_right, s.W, s.H, s.K, 1, 0, 0, p->trunc, inv_area,               \
+                                         static_cast<OT*>(cost_out), sw, stream)
     if (out_dtype == DM_F16) {
-        if (r == 1) DM_SAD_TILE(_Float16, 1);
-        else if (r == 2) DM_SAD_TILE(_Float16, 2);
-        else if (r == 3) DM_SAD_TILE(_Float16, 3);
+        if (r == 0) DM_SAD_STRIP(_Float16, 0);
+        else if (r == 1) DM_SAD_STRIP(_Float16, 1);
+        else if (r == 2) DM_SAD_STRIP(_Float16, 2);
+        else if (r == 3) DM_SAD_STRIP(_Float16, 3);
         else
             hipLaunchKernelGGL(sad_kernel<_Float16>, dim3(blocks), dim3(256), 0, stream, I_left, I_right, s.W, s.H, s.K,
                                r, p->trunc, inv_area, static_cast<_Float16*>(cost_out));
     } else {
-        if (r == 1) DM_SAD_TILE(float, 1);
-        else if (r == 2) DM_SAD_TILE(float, 2);
-        else if (r == 3) DM_SAD_TILE(float, 3);
+        if (r == 0) DM_SAD_STRIP(float, 0);
+        else if (r == 1) DM_SAD_STRIP(float, 1);
+        else if (r == 2) DM_SAD_STRIP(float, 2);
+        else if (r == 3) DM_SAD_STRIP(float, 3);
         else
             hipLaunchKernelGGL(sad_kernel<float>, dim3(blocks), dim3(256), 0, stream, I_left, I_right, s.W, s.H, s.K, r,
                                p->trunc, inv_area, static_cast<float*>(cost_out));
     }
-#undef DM_SAD_TILE
+#undef DM_SAD_STRIP
+    DM_HIP_TRY(strip, "sad strip launch");
     ps.stop();
     DM_HIP_TRY(hipGetLastError(), "sad launch");
-    if (w_h != nullptr || w_v != nullptr) {
-        const long long npx = (long long)s.W * s.H;
-        const unsigned b2 = (unsigned)std::min<long long>((npx + 255) / 256, 65535LL);
-        hipLaunchKernelGGL(contrast_kernel, dim3(b2), dim3(256), 0, stream, I_left, s.W, s.H, p->lambda_pw,
-                           1.0f / p->contrast_sigma, w_h, w_v);
-        DM_HIP_TRY(hipGetLastError(), "contrast launch");
-    }
+    if (r > 3 && (w_h != nullptr || w_v != nullptr))  // the strips wrote them otherwise
+        DM_HIP_TRY(launch_contrast_weights(I_left, s.W, s.H, p->lambda_pw, 1.0f / p->contrast_sigma, w_h, w_v, stream),
+                   "contrast launch");
     return DM_OK;
 }
