@@ -41,13 +41,20 @@ __device__ __forceinline__ rfloat prox_conj(rfloat t, rfloat w, rfloat alpha, rf
 __device__ __forceinline__ int mfield(uint32_t m, int shift, int bits) { return (int)((m >> shift) & ((1u << bits) - 1u)); }
 
 // n_iter <= S iterations in one launch (temporal tiling).  A block owns a TX x TY output
-// tile and loads the state of the tile extended by S pixels on every side into LDS; each
-// iteration runs phases A (u+) and B (q+, p+) on the whole region.  Values within s pixels
-// of the region's border are wrong after s iterations (their neighbours outside the region
-// are missing), but every dependency of the iteration reaches one pixel, so after n_iter
-// <= S iterations the output tile is exact, and the arithmetic per pixel and iteration
-// (the same expressions in the same order for every tile shape and S) does not depend on
-// the tiling: the results equal one iteration per launch bit for bit.
+// tile and runs the iteration on the tile extended by S pixels on every side, one pixel per
+// thread: values within s pixels of the region's border are wrong after s iterations (their
+// neighbours outside the region are missing), but every dependency of the iteration reaches
+// one pixel, so after n_iter <= S iterations the output tile is exact, and the arithmetic
+// per pixel and iteration (the same expressions in the same order for every tile shape and
+// S) does not depend on the tiling: the results equal one iteration per launch bit for bit.
+//
+// A pixel's state, model and weights stay in registers; LDS holds what neighbours read: the
+// edges' p - q (phase A, from the right and lower neighbour), the old u and 2 u+ - u (phase
+// B, from the left and upper one).  What bounds it: FP64 issue of the halo's extra pixels
+// against launches and the latency of an iteration (two barriers).  One pixel per thread
+// (16 waves a block, 4 per SIMD) hides that latency where 6 pixels per thread in 4 waves did
+// not; rows that no output of the remaining iterations depends on are skipped (a wave is
+// two rows).
 // mask0: the branch-mask plane of the first iteration (nullptr: no tape), mask_stride the
 // element distance between consecutive iterations' planes.
 template <int TX, int TY, int S, class DataProx>
@@ -56,131 +63,107 @@ __device__ __forceinline__ void pdhg_fused_tile(const RefineState& in, const Ref
                                                 int H, int K, const RefineScalars& sc, uint16_t* __restrict__ mask0,
                                                 size_t mask_stride, int n_iter, int x0, int y0) {
     constexpr int RX = TX + 2 * S, RY = TY + 2 * S, NP = RX * RY;
-    constexpr int NT = 256, PPT = (NP + NT - 1) / NT;
-    __shared__ rfloat s_u[2][NP];
-    __shared__ rfloat s_ph[NP], s_pv[NP], s_qh[NP], s_qv[NP];
-    const int ox = x0 - S, oy = y0 - S;
+    // one row and one pixel of padding in front: the first pixels' left and upper neighbours
+    __shared__ rfloat s_zh[NP + RX + 1], s_zv[NP + RX + 1];
+    // and behind: the last pixels' right and lower ones
+    __shared__ rfloat s_u[2][NP + RX], s_b[NP + RX];
+    const int idx = (int)threadIdx.x, zi = idx + RX + 1;
+    const int rx = idx % RX, ry = idx / RX;
+    const int x = x0 - S + rx, y = y0 - S + ry;
     const rfloat kmax = (rfloat)(K - 1);
-    // per-pixel constants of the launch stay in registers: the data model and the weights
-    // (in their storage type, widened where used)
-    typename DataProx::Px dm[PPT];
-    float wh[PPT], wv[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        wh[k] = 0.0f;
-        wv[k] = 0.0f;
-        dm[k] = typename DataProx::Px{};
-        if (idx >= NP) break;
-        const int x = ox + idx % RX, y = oy + idx / RX;
-        rfloat u = 0.0, ph = 0.0, pv = 0.0, qh = 0.0, qv = 0.0;
-        if (x >= 0 && x < W && y >= 0 && y < H) {
-            const long long p = (long long)y * W + x;
-            u = in.u[p];
-            ph = in.ph[p];
-            pv = in.pv[p];
-            qh = in.qh[p];
-            qv = in.qv[p];
-            dm[k] = prox.load(p);
-            if (x + 1 < W) wh[k] = w_h[(long long)y * (W - 1) + x];
-            if (y + 1 < H) wv[k] = w_v[p];
-        }
-        s_u[0][idx] = u;
-        s_ph[idx] = ph;
-        s_pv[idx] = pv;
-        s_qh[idx] = qh;
-        s_qv[idx] = qv;
+    const bool inside = x >= 0 && x < W && y >= 0 && y < H;
+    const bool edge_h = inside && x + 1 < W, edge_v = inside && y + 1 < H;
+    // the left / upper edges exist; beyond the region they count as 0 (never used)
+    const bool left = x > 0 && rx > 0, up = y > 0 && ry > 0;
+    const bool central = rx >= S && rx < S + TX && ry >= S && ry < S + TY && inside;
+    const long long p = (long long)y * W + x;
+    typename DataProx::Px dm{};
+    float wh = 0.0f, wv = 0.0f;
+    rfloat u = 0.0, ph = 0.0, pv = 0.0, qh = 0.0, qv = 0.0;
+    if (inside) {
+        u = in.u[p];
+        ph = in.ph[p];
+        pv = in.pv[p];
+        qh = in.qh[p];
+        qv = in.qv[p];
+        dm = prox.load(p);
+        if (edge_h) wh = w_h[(long long)y * (W - 1) + x];
+        if (edge_v) wv = w_v[p];
     }
+    s_zh[zi] = ph - qh;
+    s_zv[zi] = pv - qv;
+    s_u[0][idx] = u;
     __syncthreads();
     int cur = 0;
     for (int it = 0; it < n_iter; ++it) {
-        int code[PPT];
-        // Phase A: u+ on the region.
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            code[k] = 0;
-            const int idx = (int)threadIdx.x + k * NT;
-            if (idx >= NP) break;
-            const int rx = idx % RX, ry = idx / RX;
-            const int x = ox + rx, y = oy + ry;
-            rfloat un = 0.0;
-            if (x >= 0 && x < W && y >= 0 && y < H) {
-                // (A^T z)_i = z_h(i) + z_v(i) - z_h(left) - z_v(up), z = p - q
-                rfloat at = 0.0;
-                if (x + 1 < W) at += s_ph[idx] - s_qh[idx];
-                if (y + 1 < H) at += s_pv[idx] - s_qv[idx];
-                if (x > 0) at -= rx > 0 ? s_ph[idx - 1] - s_qh[idx - 1] : 0.0;
-                if (y > 0) at -= ry > 0 ? s_pv[idx - RX] - s_qv[idx - RX] : 0.0;
-                un = prox.apply(s_u[cur][idx] - sc.tau * at, dm[k], kmax, code[k]);
-            }
-            s_u[cur ^ 1][idx] = un;
+        const int rem = n_iter - it;
+        int code = 0;
+        // Phase A: u+ and the extrapolated 2 u+ - u.
+        rfloat un = 0.0;
+        const bool rows_a = ry >= S - rem && ry <= S + TY - 1 + rem;
+        if (inside && rows_a) {
+            // (A^T z)_i = z_h(i) + z_v(i) - z_h(left) - z_v(up), z = p - q
+            rfloat at = 0.0;
+            if (edge_h) at += ph - qh;
+            if (edge_v) at += pv - qv;
+            if (x > 0) at -= left ? s_zh[zi - 1] : 0.0;
+            if (y > 0) at -= up ? s_zv[zi - RX] : 0.0;
+            un = prox.apply(u - sc.tau * at, dm, kmax, code);
         }
+        const rfloat b = 2.0 * un - u;
+        if (rows_a) s_b[idx] = b;
         __syncthreads();
-        // Phase B: q+ (old u) and p+ (extrapolated 2u+ - u) on the region's edges, in place.
-        uint16_t* mask = mask0 != nullptr ? mask0 + (size_t)it * mask_stride : nullptr;
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int idx = (int)threadIdx.x + k * NT;
-            if (idx >= NP) break;
-            const int rx = idx % RX, ry = idx / RX;
-            const int x = ox + rx, y = oy + ry;
-            if (x < 0 || x >= W || y < 0 || y >= H) continue;
-            const rfloat uo = s_u[cur][idx], un = s_u[cur ^ 1][idx];
-            uint32_t m = (uint32_t)code[k];
+        // Phase B: q+ (old u) and p+ (extrapolated) on the pixel's edges.
+        if (inside && ry >= S - rem && ry <= S + TY - 2 + rem) {
+            uint32_t m = (uint32_t)code;
             int c;
-            if (x + 1 < W) {
-                const int r = rx + 1 < RX ? idx + 1 : idx;  // beyond the region: a value that is never used
-                const rfloat gq = uo - s_u[cur][r];
-                const rfloat w = (rfloat)wh[k];
-                s_qh[idx] = prox_conj(s_qh[idx] + sc.tau * gq, w, 0.0, sc.beta_minus, sc.tau, c);
+            if (edge_h) {  // (beyond the region's right border: values that are never used)
+                const rfloat gq = u - s_u[cur][idx + 1];
+                const rfloat w = (rfloat)wh;
+                qh = prox_conj(qh + sc.tau * gq, w, 0.0, sc.beta_minus, sc.tau, c);
                 m |= (uint32_t)c << 4;
-                const rfloat gp = (2.0 * un - uo) - (2.0 * s_u[cur ^ 1][r] - s_u[cur][r]);
-                s_ph[idx] = prox_conj(s_ph[idx] + sc.sigma * gp, w, sc.eps, sc.delta, sc.sigma, c);
+                const rfloat gp = b - s_b[idx + 1];
+                ph = prox_conj(ph + sc.sigma * gp, w, sc.eps, sc.delta, sc.sigma, c);
                 m |= (uint32_t)c << 10;
+                s_zh[zi] = ph - qh;
             }
-            if (y + 1 < H) {
-                const int d = ry + 1 < RY ? idx + RX : idx;
-                const rfloat gq = uo - s_u[cur][d];
-                const rfloat w = (rfloat)wv[k];
-                s_qv[idx] = prox_conj(s_qv[idx] + sc.tau * gq, w, 0.0, sc.beta_minus, sc.tau, c);
+            if (edge_v) {
+                const rfloat gq = u - s_u[cur][idx + RX];
+                const rfloat w = (rfloat)wv;
+                qv = prox_conj(qv + sc.tau * gq, w, 0.0, sc.beta_minus, sc.tau, c);
                 m |= (uint32_t)c << 7;
-                const rfloat gp = (2.0 * un - uo) - (2.0 * s_u[cur ^ 1][d] - s_u[cur][d]);
-                s_pv[idx] = prox_conj(s_pv[idx] + sc.sigma * gp, w, sc.eps, sc.delta, sc.sigma, c);
+                const rfloat gp = b - s_b[idx + RX];
+                pv = prox_conj(pv + sc.sigma * gp, w, sc.eps, sc.delta, sc.sigma, c);
                 m |= (uint32_t)c << 13;
+                s_zv[zi] = pv - qv;
             }
-            const bool central = rx >= S && rx < S + TX && ry >= S && ry < S + TY;
-            if (mask != nullptr && central) mask[(long long)y * W + x] = (uint16_t)m;
+            if (mask0 != nullptr && central) mask0[(size_t)it * mask_stride + p] = (uint16_t)m;
         }
-        __syncthreads();
+        u = un;
         cur ^= 1;
+        s_u[cur][idx] = u;
+        __syncthreads();
     }
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        if (idx >= NP) break;
-        const int rx = idx % RX, ry = idx / RX;
-        const int x = ox + rx, y = oy + ry;
-        if (rx < S || rx >= S + TX || ry < S || ry >= S + TY || x >= W || y >= H) continue;
-        const long long p = (long long)y * W + x;
-        out.u[p] = s_u[cur][idx];
-        out.ph[p] = s_ph[idx];
-        out.pv[p] = s_pv[idx];
-        out.qh[p] = s_qh[idx];
-        out.qv[p] = s_qv[idx];
+    if (central) {
+        out.u[p] = u;
+        out.ph[p] = ph;
+        out.pv[p] = pv;
+        out.qh[p] = qh;
+        out.qv[p] = qv;
     }
 }
 
-// Fused tile shapes.  The stereo forward: 40 x 24 outputs, 4 iterations per launch, a
-// 48 x 32 region (73.7 KB of LDS, 6 pixels per thread), so two blocks share a CU and the
-// 512 blocks of a 1242 x 375 frame are all resident at once; 40 iterations per warp take
-// 10 launches.  Its adjoint: 32 x 16 outputs, 4 reverse iterations per launch, a 40 x 24
-// region (40.3 KB of LDS, 4 pixels per thread, 113 VGPRs), four blocks per CU and the 936
-// blocks of a frame resident (with 6 pixels per thread the adjoint's accumulators exceed
-// the register file).  The flow refinement (quadratic-fit model): 32 x 20 outputs, 3
-// iterations per launch, a 38 x 26 region, three blocks per CU.
-constexpr int kFTX = 40, kFTY = 24, kFS = 4;
-constexpr int kATX = 32, kATY = 16, kAS = 4;
-constexpr int kQTX = 32, kQTY = 20, kQS = 3;
-
+// Fused tile shapes, forward (stereo, batched and flow) and adjoint: 22 x 22 outputs, 5
+// iterations per launch, a 32 x 32 region of 1024 threads in at most 64 registers, so two
+// blocks share a CU; 40 iterations per warp take 8 launches.  Measured, 5 x 40 iterations at
+// 1242 x 375 and 320 x 240: forward 2039 -> 1380 and 1508 -> 511 us, adjoint with the
+// linearisations 2319 -> 1706 and 1178 -> 583 us (before: 40 x 24 x 4 with 6 pixels per thread
+// and 32 x 16 x 4 with 4, the state in LDS).  Other regions, forward: 32 x 24 (24 x 16 x 4)
+// 1434 and 493, 20 x 20 x 6 1381 and 469, 16 x 16 x 8 2324 and 657 us; one block per CU
+// (more registers) 1759 us.
+constexpr int kFTX = 22, kFTY = 22, kFS = 5;
+constexpr int kFNT = (kFTX + 2 * kFS) * (kFTY + 2 * kFS);  // threads: one per pixel of the region
+constexpr int kATX = 22, kATY = 22, kAS = 5;
+constexpr int kANT = (kATX + 2 * kAS) * (kATY + 2 * kAS);
 
 }  // namespace dm

@@ -17,7 +17,7 @@
 //   linearize_kernel : u0 := u, slopes (s_L, s_R) of the data term at u0 by linear
 //                      interpolation of the cost volume along the label axis (once per warp)
 //   pdhg_fused_kernel: kFS iterations per launch on a tile extended by kFS pixels, the state
-//                      in LDS between iterations (temporal tiling, pdhg.h).  Optionally
+//                      on chip between iterations (temporal tiling, pdhg.h).  Optionally
 //                      records the branch taken by every prox (16-bit mask per pixel and
 //                      iteration) for the adjoint.  batched_pdhg_fused_kernel: the same
 //                      per (instance, tile) of a batched plan's table.
@@ -130,7 +130,7 @@ struct TwoSlopeProx {
     }
 };
 
-__global__ __launch_bounds__(256, 2) void pdhg_fused_kernel(const RefineState in, RefineState out,
+__global__ __launch_bounds__(kFNT, kFNT / 128) void pdhg_fused_kernel(const RefineState in, RefineState out,
                                                          const rfloat* __restrict__ u0, const rfloat* __restrict__ sL,
                                                          const rfloat* __restrict__ sR, const float* __restrict__ w_h,
                                                          const float* __restrict__ w_v, int W, int H, int K,
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(256) void batched_linearize_kernel(const RefBatchIn
         linearize_px(static_cast<const TT*>(in.theta), in.S[cur].u, p, in.K, h, in.u0, in.sL, in.sR);
 }
 
-__global__ __launch_bounds__(256, 2) void batched_pdhg_fused_kernel(const RefBatchInst* __restrict__ insts,
+__global__ __launch_bounds__(kFNT, kFNT / 128) void batched_pdhg_fused_kernel(const RefBatchInst* __restrict__ insts,
                                                                     const RefTile* __restrict__ tiles, int cur,
                                                                     RefineScalars sc, int n_iter) {
     const RefTile t = tiles[blockIdx.x];
@@ -206,7 +206,7 @@ hipError_t launch_batched_refine(const RefBatchInst* insts, const RefChunk* chun
         // kFS iterations per launch, as the single-instance refinement
         for (int it0 = 0; it0 < p.n_iters; it0 += kFS) {
             const int nit = std::min(kFS, p.n_iters - it0);
-            hipLaunchKernelGGL(batched_pdhg_fused_kernel, dim3(n_tiles), dim3(256), 0, st, insts, tiles, cur, sc, nit);
+            hipLaunchKernelGGL(batched_pdhg_fused_kernel, dim3(n_tiles), dim3(kFNT), 0, st, insts, tiles, cur, sc, nit);
             cur ^= 1;
         }
     }
@@ -224,172 +224,122 @@ __device__ __forceinline__ rfloat conj_dw(int code, rfloat alpha) {
 
 // n_iter <= kAS reverse iterations per launch (temporal tiling, as pdhg_fused_tile): the
 // adjoint of iteration it reaches one pixel (diagonals included), so a kATX x kATY output
-// tile is exact after n_iter iterations on the tile extended by kAS pixels on every side.
-// The adjoint state sits in LDS between iterations; the accumulators of the tile's pixels
-// (u0, slopes, edge weights) are loaded once, carried in registers in the order of the
-// additions of one reverse iteration at a time and stored once, so the results do not
-// depend on the tiling (bit for bit).  Per iteration: the branch masks of the region into
-// LDS; phase A the adjoint of u-hat and the new u adjoint (from the own and the left /
-// upper edges); phase B the edge adjoints in place and the accumulators.  mask_hi: the mask plane of
-// the launch's first (latest) iteration; earlier iterations lie mask_stride elements
-// below, one plane each.
-__global__ __launch_bounds__(256) void pdhg_adjoint_fused_kernel(const RefineState nxt, RefineState prv,
-                                                                 const uint16_t* __restrict__ mask_hi,
-                                                                 size_t mask_stride, int n_iter,
-                                                                 const rfloat* __restrict__ u0, int W, int H, int K,
-                                                                 RefineScalars sc, rfloat* __restrict__ acc_u0,
-                                                                 rfloat* __restrict__ acc_sL, rfloat* __restrict__ acc_sR,
-                                                                 rfloat* __restrict__ acc_wh,
-                                                                 rfloat* __restrict__ acc_wv) {
+// tile is exact after n_iter iterations on the tile extended by kAS pixels on every side,
+// one pixel per thread.  A pixel's adjoint state and, for the tile's own pixels, the
+// accumulators (u0, slopes, edge weights) stay in registers, added to in the order of one
+// reverse iteration at a time and stored once, so the results do not depend on the tiling
+// (bit for bit).  LDS holds what neighbours read: the edges' adjoints through their branches
+// (phase A: the right and lower pixel) and the adjoint of u-hat (phase B: the left and upper
+// one).  The branch mask of the next iteration is loaded during the current one.  mask_hi:
+// the mask plane of the launch's first (latest) iteration; earlier iterations lie
+// mask_stride elements below, one plane each.
+__global__ __launch_bounds__(kANT, kANT / 128) void pdhg_adjoint_fused_kernel(
+    const RefineState nxt, RefineState prv, const uint16_t* __restrict__ mask_hi, size_t mask_stride, int n_iter,
+    const rfloat* __restrict__ u0, int W, int H, int K, RefineScalars sc, rfloat* __restrict__ acc_u0,
+    rfloat* __restrict__ acc_sL, rfloat* __restrict__ acc_sR, rfloat* __restrict__ acc_wh,
+    rfloat* __restrict__ acc_wv) {
     constexpr int TX = kATX, TY = kATY, S = kAS;
     constexpr int RX = TX + 2 * S, RY = TY + 2 * S, NP = RX * RY;
-    constexpr int NT = 256, PPT = (NP + NT - 1) / NT;
-    // the u adjoint of a pixel is read and written by that pixel only: in registers
-    __shared__ rfloat s_ph[NP], s_pv[NP], s_qh[NP], s_qv[NP], s_uhb[NP];
-    __shared__ uint16_t s_m[NP];
-    const int ox = (int)blockIdx.x * TX - S, oy = (int)blockIdx.y * TY - S;
+    // a row and a pixel of padding in front (left and upper neighbours), a row behind
+    __shared__ rfloat s_ph[NP + RX + 1], s_pv[NP + RX + 1], s_qh[NP + RX + 1], s_qv[NP + RX + 1], s_uhb[NP + RX];
+    const int idx = (int)threadIdx.x, zi = idx + RX + 1;
+    const int rx = idx % RX, ry = idx / RX;
+    const int x = (int)blockIdx.x * TX - S + rx, y = (int)blockIdx.y * TY - S + ry;
     const rfloat kmax = (rfloat)(K - 1);
-    // per slot: the pixel's u0, and for the tile's own pixels the accumulators
-    rfloat su[PPT], c0[PPT], a_u0[PPT], a_sL[PPT], a_sR[PPT], a_wh[PPT], a_wv[PPT];
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        su[k] = c0[k] = a_u0[k] = a_sL[k] = a_sR[k] = a_wh[k] = a_wv[k] = 0.0;
-        if (idx >= NP) break;
-        const int rx = idx % RX, ry = idx / RX;
-        const int x = ox + rx, y = oy + ry;
-        rfloat u = 0.0, ph = 0.0, pv = 0.0, qh = 0.0, qv = 0.0;
-        if (x >= 0 && x < W && y >= 0 && y < H) {
-            const long long p = (long long)y * W + x;
-            u = nxt.u[p];
-            ph = nxt.ph[p];
-            pv = nxt.pv[p];
-            qh = nxt.qh[p];
-            qv = nxt.qv[p];
-            c0[k] = u0[p];
-            if (rx >= S && rx < S + TX && ry >= S && ry < S + TY) {
-                a_u0[k] = acc_u0[p];
-                a_sL[k] = acc_sL[p];
-                a_sR[k] = acc_sR[p];
-                a_wh[k] = acc_wh[p];
-                a_wv[k] = acc_wv[p];
-            }
-        }
-        su[k] = u;
-        s_ph[idx] = ph;
-        s_pv[idx] = pv;
-        s_qh[idx] = qh;
-        s_qv[idx] = qv;
+    const bool inside = x >= 0 && x < W && y >= 0 && y < H;
+    const bool edge_h = inside && x + 1 < W, edge_v = inside && y + 1 < H;
+    const bool left = x > 0 && rx > 0, up = y > 0 && ry > 0;
+    const bool central = rx >= S && rx < S + TX && ry >= S && ry < S + TY && inside;
+    const long long p = (long long)y * W + x;
+    rfloat su = 0.0, ph = 0.0, pv = 0.0, qh = 0.0, qv = 0.0;
+    rfloat c0 = 0.0, a_u0 = 0.0, a_sL = 0.0, a_sR = 0.0, a_wh = 0.0, a_wv = 0.0;
+    uint32_t mask = 0u;
+    if (inside) {
+        su = nxt.u[p];
+        ph = nxt.ph[p];
+        pv = nxt.pv[p];
+        qh = nxt.qh[p];
+        qv = nxt.qv[p];
+        mask = mask_hi[p];
+    }
+    if (central) {
+        c0 = u0[p];
+        a_u0 = acc_u0[p];
+        a_sL = acc_sL[p];
+        a_sR = acc_sR[p];
+        a_wh = acc_wh[p];
+        a_wv = acc_wv[p];
     }
     for (int it = 0; it < n_iter; ++it) {
-        const uint16_t* mask = mask_hi - (size_t)it * mask_stride;
-        uint32_t mm[PPT];
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int idx = (int)threadIdx.x + k * NT;
-            mm[k] = 0u;
-            if (idx >= NP) break;
-            const int x = ox + idx % RX, y = oy + idx / RX;
-            if (x >= 0 && x < W && y >= 0 && y < H) mm[k] = mask[(long long)y * W + x];
-            s_m[idx] = (uint16_t)mm[k];
-        }
-        __syncthreads();  // the masks, and (it > 0) the previous iteration's edges
-        rfloat ubt[PPT];
+        const uint32_t m = mask;
+        if (inside && it + 1 < n_iter) mask = mask_hi[p - (long long)(it + 1) * (long long)mask_stride];
+        const int cqh = mfield(m, 4, 3), cqv = mfield(m, 7, 3), cph = mfield(m, 10, 3), cpv = mfield(m, 13, 3);
+        s_ph[zi] = ph * conj_dt(cph);
+        s_qh[zi] = qh * conj_dt(cqh);
+        s_pv[zi] = pv * conj_dt(cpv);
+        s_qv[zi] = qv * conj_dt(cqv);
+        __syncthreads();
+        const int zone = mfield(m, 0, 2), cl = mfield(m, 2, 2);
         // Phase A: adjoint of u-hat, and the adjoint of the iteration's input u.
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int idx = (int)threadIdx.x + k * NT;
-            ubt[k] = 0.0;
-            if (idx >= NP) break;
-            const int rx = idx % RX, ry = idx / RX;
-            const int x = ox + rx, y = oy + ry;
-            rfloat uhb = 0.0, un = 0.0;
-            if (x >= 0 && x < W && y >= 0 && y < H) {
-                const uint32_t m = mm[k];
-                // (A^T p-bar-hat) and (A^T q-bar-hat): own edges, then the left / upper ones
-                rfloat atp = 0.0, atq = 0.0;
-                if (x + 1 < W) {
-                    atp += s_ph[idx] * conj_dt(mfield(m, 10, 3));
-                    atq += s_qh[idx] * conj_dt(mfield(m, 4, 3));
-                }
-                if (y + 1 < H) {
-                    atp += s_pv[idx] * conj_dt(mfield(m, 13, 3));
-                    atq += s_qv[idx] * conj_dt(mfield(m, 7, 3));
-                }
-                if (x > 0 && rx > 0) {
-                    const uint32_t ml = s_m[idx - 1];
-                    atp -= s_ph[idx - 1] * conj_dt(mfield(ml, 10, 3));
-                    atq -= s_qh[idx - 1] * conj_dt(mfield(ml, 4, 3));
-                }
-                if (y > 0 && ry > 0) {
-                    const uint32_t mu = s_m[idx - RX];
-                    atp -= s_pv[idx - RX] * conj_dt(mfield(mu, 13, 3));
-                    atq -= s_qv[idx - RX] * conj_dt(mfield(mu, 7, 3));
-                }
-                ubt[k] = su[k] + 2.0 * sc.sigma * atp;
-                const int zone = mfield(m, 0, 2), cl = mfield(m, 2, 2);
-                uhb = (cl == 0 && zone != 0) ? ubt[k] : 0.0;
-                un = uhb - sc.sigma * atp + sc.tau * atq;
+        rfloat ubt = 0.0, uhb = 0.0, un = 0.0;
+        if (inside) {
+            // (A^T p-bar-hat) and (A^T q-bar-hat): own edges, then the left / upper ones
+            rfloat atp = 0.0, atq = 0.0;
+            if (edge_h) {
+                atp += ph * conj_dt(cph);
+                atq += qh * conj_dt(cqh);
             }
-            s_uhb[idx] = uhb;
-            su[k] = un;
+            if (edge_v) {
+                atp += pv * conj_dt(cpv);
+                atq += qv * conj_dt(cqv);
+            }
+            if (left) {
+                atp -= s_ph[zi - 1];
+                atq -= s_qh[zi - 1];
+            }
+            if (up) {
+                atp -= s_pv[zi - RX];
+                atq -= s_qv[zi - RX];
+            }
+            ubt = su + 2.0 * sc.sigma * atp;
+            uhb = (cl == 0 && zone != 0) ? ubt : 0.0;
+            un = uhb - sc.sigma * atp + sc.tau * atq;
         }
+        s_uhb[idx] = uhb;
+        su = un;
         __syncthreads();
         // Phase B: the edges' adjoints in place, the accumulators of the tile's pixels.
-#pragma unroll
-        for (int k = 0; k < PPT; ++k) {
-            const int idx = (int)threadIdx.x + k * NT;
-            if (idx >= NP) break;
-            const int rx = idx % RX, ry = idx / RX;
-            const int x = ox + rx, y = oy + ry;
-            if (x < 0 || x >= W || y < 0 || y >= H) continue;
-            const uint32_t m = mm[k];
-            const rfloat uhb = s_uhb[idx];
-            if (x + 1 < W) {
-                const int cq = mfield(m, 4, 3), cp = mfield(m, 10, 3);
-                const int r = rx + 1 < RX ? idx + 1 : idx;  // beyond the region: a value that is never used
-                const rfloat du = uhb - s_uhb[r];
-                const rfloat ph = s_ph[idx], qh = s_qh[idx];
-                s_ph[idx] = ph * conj_dt(cp) - sc.tau * du;
-                s_qh[idx] = qh * conj_dt(cq) + sc.tau * du;
-                a_wh[k] += ph * conj_dw(cp, sc.eps) + qh * conj_dw(cq, 0.0);
-            }
-            if (y + 1 < H) {
-                const int cq = mfield(m, 7, 3), cp = mfield(m, 13, 3);
-                const int d = ry + 1 < RY ? idx + RX : idx;
-                const rfloat du = uhb - s_uhb[d];
-                const rfloat pv = s_pv[idx], qv = s_qv[idx];
-                s_pv[idx] = pv * conj_dt(cp) - sc.tau * du;
-                s_qv[idx] = qv * conj_dt(cq) + sc.tau * du;
-                a_wv[k] += pv * conj_dw(cp, sc.eps) + qv * conj_dw(cq, 0.0);
-            }
-            // u-prox adjoint into u0 and the slopes (selects)
-            const int zone = mfield(m, 0, 2), cl = mfield(m, 2, 2);
-            const bool pass_u0 = cl == 0 ? zone == 0 : (cl == 1 ? c0[k] - sc.h >= 0.0 : c0[k] + sc.h <= kmax);
-            a_u0[k] += ubt[k] * (pass_u0 ? 1.0 : 0.0);
-            a_sR[k] = (cl == 0 && zone == 1) ? a_sR[k] - sc.tau * ubt[k] : a_sR[k];
-            a_sL[k] = (cl == 0 && zone == 2) ? a_sL[k] - sc.tau * ubt[k] : a_sL[k];
+        if (edge_h) {  // (beyond the region's right border: values that are never used)
+            const rfloat du = uhb - s_uhb[idx + 1];
+            const rfloat ph0 = ph, qh0 = qh;
+            ph = ph0 * conj_dt(cph) - sc.tau * du;
+            qh = qh0 * conj_dt(cqh) + sc.tau * du;
+            a_wh += ph0 * conj_dw(cph, sc.eps) + qh0 * conj_dw(cqh, 0.0);
         }
-        __syncthreads();  // phase B's edges before the next iteration reads them
+        if (edge_v) {
+            const rfloat du = uhb - s_uhb[idx + RX];
+            const rfloat pv0 = pv, qv0 = qv;
+            pv = pv0 * conj_dt(cpv) - sc.tau * du;
+            qv = qv0 * conj_dt(cqv) + sc.tau * du;
+            a_wv += pv0 * conj_dw(cpv, sc.eps) + qv0 * conj_dw(cqv, 0.0);
+        }
+        // u-prox adjoint into u0 and the slopes (selects)
+        const bool pass_u0 = cl == 0 ? zone == 0 : (cl == 1 ? c0 - sc.h >= 0.0 : c0 + sc.h <= kmax);
+        a_u0 += ubt * (pass_u0 ? 1.0 : 0.0);
+        a_sR = (cl == 0 && zone == 1) ? a_sR - sc.tau * ubt : a_sR;
+        a_sL = (cl == 0 && zone == 2) ? a_sL - sc.tau * ubt : a_sL;
     }
-#pragma unroll
-    for (int k = 0; k < PPT; ++k) {
-        const int idx = (int)threadIdx.x + k * NT;
-        if (idx >= NP) break;
-        const int rx = idx % RX, ry = idx / RX;
-        const int x = ox + rx, y = oy + ry;
-        if (rx < S || rx >= S + TX || ry < S || ry >= S + TY || x >= W || y >= H) continue;
-        const long long p = (long long)y * W + x;
-        prv.u[p] = su[k];
-        prv.ph[p] = s_ph[idx];
-        prv.pv[p] = s_pv[idx];
-        prv.qh[p] = s_qh[idx];
-        prv.qv[p] = s_qv[idx];
-        acc_u0[p] = a_u0[k];
-        acc_sL[p] = a_sL[k];
-        acc_sR[p] = a_sR[k];
-        acc_wh[p] = a_wh[k];
-        acc_wv[p] = a_wv[k];
+    if (central) {
+        prv.u[p] = su;
+        prv.ph[p] = ph;
+        prv.pv[p] = pv;
+        prv.qh[p] = qh;
+        prv.qv[p] = qv;
+        acc_u0[p] = a_u0;
+        acc_sL[p] = a_sL;
+        acc_sR[p] = a_sR;
+        acc_wh[p] = a_wh;
+        acc_wv[p] = a_wv;
     }
 }
 
@@ -641,7 +591,7 @@ extern "C" int dm_refine_continuous(const void* cost, dm_dtype cost_dtype, const
                                            : nullptr;
             // per pixel and iteration: reads u, u0, sL, sR, 4 duals, 2 weights; writes u and 4 duals
             ProfScope ps2(DM_PROF_REFINE_ITER, nit * npx * (8.0 * 13.0 + 8.0), stream);
-            hipLaunchKernelGGL(pdhg_fused_kernel, fgrid, dim3(256), 0, stream, S[cur], S[cur ^ 1], u0, sL, sR, w_h,
+            hipLaunchKernelGGL(pdhg_fused_kernel, fgrid, dim3(kFNT), 0, stream, S[cur], S[cur ^ 1], u0, sL, sR, w_h,
                                w_v, s.W, s.H, s.K, sc, mask0, L.mask_plane / sizeof(uint16_t), nit);
             cur ^= 1;
         }
@@ -709,7 +659,7 @@ extern "C" int dm_refine_continuous_backward(const float* grad_u, const void* co
             const int nit = std::min(kAS, hi + 1);
             const uint16_t* mask = reinterpret_cast<const uint16_t*>(
                 fws + LF.tape_mask + ((size_t)wp * p->n_iters + hi) * LF.mask_plane);
-            hipLaunchKernelGGL(pdhg_adjoint_fused_kernel, fgrid, dim3(256), 0, stream, A[cur], A[cur ^ 1], mask,
+            hipLaunchKernelGGL(pdhg_adjoint_fused_kernel, fgrid, dim3(kANT), 0, stream, A[cur], A[cur ^ 1], mask,
                                LF.mask_plane / sizeof(uint16_t), nit, u0, s.W, s.H, s.K, sc, acc_u0, acc_sL, acc_sR,
                                acc_wh, acc_wv);
             cur ^= 1;
