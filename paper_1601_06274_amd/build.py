@@ -30,13 +30,16 @@ def _tiles(macro):
 
 TILES = _tiles("X")
 PIPE_TILES = _tiles("Y")
+PIPE_SCAN_TILES = _tiles("Z")
 UNITS = [("api.hip", [], "api"), ("dmm.hip", [], "dmm"), ("cost_volume.hip", [], "cost_volume"),
          ("refine.hip", [], "refine"), ("batched.hip", [], "batched"), ("noalloc.hip", [], "noalloc"), ("batched_grad.hip", [], "batched_grad"),
          ("flow.hip", [], "flow")]
 # largest units first so the parallel build's critical path starts early
 UNITS = [("dmm_tile.hip", [f"-DDM_TILE_G={g}", f"-DDM_TILE_L={l}", f"-DDM_TILE_PART={k}"], f"dmm_tile_{g}x{l}_{v}")
          for k, v in [(2, "adj"), (4, "tape"), (1, "fwd"), (3, "batch")] for g, l in sorted(TILES, key=lambda t: -t[0] * t[1])] + UNITS
-UNITS += [("dmm_pipe.hip", [f"-DDM_PIPE_G={g}", f"-DDM_PIPE_L={l}"], f"dmm_pipe_{g}x{l}") for g, l in reversed(PIPE_TILES)]
+UNITS = [("dmm_pipe.hip", [f"-DDM_PIPE_G={g}", f"-DDM_PIPE_L={l}", f"-DDM_PIPE_SCAN={k}"], f"dmm_pipe_{g}x{l}_{v}")
+         for k, v, tiles in [(0, "window", PIPE_TILES), (1, "scan", PIPE_SCAN_TILES)]
+         for g, l in sorted(tiles, key=lambda t: -t[1])] + UNITS
 # the hierarchical-minorant kernels, one unit per labels-per-lane count (the slowest
 # compiles: first), and their dispatch
 UNITS = ([("dmm_hier.hip", [f"-DDM_HIER_LPL={l}"], f"dmm_hier_{l}") for l in (3, 4, 2, 1)] + UNITS +

@@ -22,8 +22,11 @@ namespace dm {
     extern template hipError_t launch_adjoint_tile<g, l, true>(const AdjArgs&, dm_dtype, hipStream_t);
 DM_FOR_EACH_TILE(DM_EXTERN_TILE)
 #undef DM_EXTERN_TILE
-#define DM_EXTERN_PIPE(g, l) extern template hipError_t launch_pipe<g, l>(const SweepArgs&, dm_dtype, hipStream_t);
+#define DM_EXTERN_PIPE(g, l) extern template hipError_t launch_pipe<g, l, false>(const SweepArgs&, dm_dtype, hipStream_t);
 DM_FOR_EACH_PIPE(DM_EXTERN_PIPE)
+#undef DM_EXTERN_PIPE
+#define DM_EXTERN_PIPE(g, l) extern template hipError_t launch_pipe<g, l, true>(const SweepArgs&, dm_dtype, hipStream_t);
+DM_FOR_EACH_PIPE_SCAN(DM_EXTERN_PIPE)
 #undef DM_EXTERN_PIPE
 
 // ------------------------------------------------------------------ small kernels
@@ -187,10 +190,6 @@ __global__ __launch_bounds__(256) void bounds_kernel(const double* __restrict__ 
 // ------------------------------------------------------------------ host side
 namespace {
 
-struct Tile {
-    int G, LPL;
-};
-
 // Tiles compiled into the library; a chain of K labels needs G*LPL >= K.
 #define DM_TILE_ENTRY(g, l) {g, l},
 constexpr Tile kTiles[] = {DM_FOR_EACH_TILE(DM_TILE_ENTRY)};
@@ -234,25 +233,29 @@ hipError_t launch_tile_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_
     return hipErrorInvalidValue;
 }
 
-// The pipelined sweep's tile for a launch, {0, 0} where the one-wave tile kernel is used.
-// The two give the same results bit for bit where the tile's message is the direct window
-// (T <= 3 and its reach within one lane); the scans of larger T round by tile.  The line lies
-// at one workgroup per slot of the chip (by LDS): beyond it a second round of workgroups costs
-// as much again, while the one-wave kernel is at HBM bandwidth (1242 columns of K = 192: 826 us
-// against about 2 x 600).
-Tile pipe_tile(Tile t, const SweepArgs& a) {
-    if ((a.mode & kRecordFlag) != 0 || a.T > 3 || a.T - 1 > t.LPL) return Tile{0, 0};
-    const Tile d = a.K <= 16 ? Tile{16, 1} : (a.K <= 32 ? Tile{32, 1} : Tile{64, (a.K + 63) / 64});
+// Whether the pipelined sweeps serve a launch on tile d: its workgroups are all resident.
+// Beyond that a second round of workgroups costs as much again, while the one-wave kernel is
+// at HBM bandwidth (1242 columns of K = 192: 826 us against about 2 x 600).
+bool pipe_fits(Tile d, const SweepArgs& a) {
     const int blocks = (a.n_chains + 64 / d.G - 1) / (64 / d.G);
-    return blocks <= pipe_resident(d.LPL, a.theta != nullptr) ? d : Tile{0, 0};
+    return (a.mode & kRecordFlag) == 0 && blocks <= pipe_resident(d.LPL, a.theta != nullptr);
 }
 
 hipError_t launch_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st) {
-    const Tile d = pipe_tile(t, a);
+    if (a.T <= 3 && a.T - 1 <= t.LPL) {
+        // the tile's message is the direct window: the same results bit for bit on any tile
+        const Tile d = window_tile(a.K);
 #define DM_PIPE_CASE(g, l) \
-    if (d.G == g && d.LPL == l) return launch_pipe<g, l>(a, dt, st);
-    DM_FOR_EACH_PIPE(DM_PIPE_CASE)
+    if (d.G == g && d.LPL == l && pipe_fits(d, a)) return launch_pipe<g, l, false>(a, dt, st);
+        DM_FOR_EACH_PIPE(DM_PIPE_CASE)
 #undef DM_PIPE_CASE
+    } else {
+        // the scans round by tile: the same tile
+#define DM_PIPE_CASE(g, l) \
+    if (t.G == g && t.LPL == l && pipe_fits(t, a)) return launch_pipe<g, l, true>(a, dt, st);
+        DM_FOR_EACH_PIPE_SCAN(DM_PIPE_CASE)
+#undef DM_PIPE_CASE
+    }
     return launch_tile_sweep(t, a, dt, st);
 }
 

@@ -24,7 +24,8 @@
 // 198 -> 102 us (155 -> 80 ns a node), 128x96, K = 32 88 -> 55 us; with all of a large frame's
 // traffic to HBM the gain is what bandwidth leaves: 640x480, K = 128, FP32 rows 534 -> 424 us
 // (6.3 TB/s), 1242x375, K = 192, FP16 rows 1130 -> 1074 us.  The chain wave alone takes 72,
-// 106, 128 ns a node at 1, 2, 3 labels per lane.
+// 106, 128 ns a node at 1, 2, 3 labels per lane.  Messages by scans (T > 3), whole solve of
+// 611x437, K = 100, T = 6: 5.91 -> 5.10 ms.
 //
 // The arithmetic of every value is chain_kernel's, operation for operation, so the results
 // are the same bit for bit, whatever tile (lanes, labels per lane) either uses.
@@ -139,7 +140,8 @@ constexpr int pipe_intervals(int n_chunks) { return n_chunks + 3; }
 
 // ------------------------------------------------------------------ chain wave
 // KIND as in Walker::pass: 0 message pass, 1 iterative update, 2 naive update, 3 final.
-template <int G, int LPL, bool T3, bool HAS_THETA>
+// MF: message form as there - 0 scans, 2 direct window, 3 direct window with T = 3.
+template <int G, int LPL, int MF, bool HAS_THETA>
 struct PipeChain {
     static constexpr int C = pipe_chunk(LPL);
     static constexpr int NIN = pipe_in_words(LPL, HAS_THETA), NOUT = pipe_out_words(LPL);
@@ -147,6 +149,7 @@ struct PipeChain {
     PipeRec<NOUT, 2 * C> out;
     const lds_u32* wgt;  // this group's edge weights
     int lane, sub, T;
+    int dt_steps;  // scans: lanes that the truncation reaches across
     bool lv[LPL];  // label exists
     // lane shifts: lanes without a source keep kBig
     float dl, dr, dl2, dr2, b15, b31;
@@ -183,10 +186,32 @@ struct PipeChain {
         return group_min<G>(x);
     }
 
-    // The direct window message (Walker::message_direct) without the cap and the
+    // The message (Walker::message_direct, Walker::message) without the cap and the
     // normalisation, so that it does not wait for the minimum.  Labels that do not exist
     // hold kBig in v, so no window takes them, and what comes out at them is never used.
     __device__ __forceinline__ void window(const float (&v)[LPL], float wt, float (&e)[LPL]) {
+        if constexpr (MF == 0) {
+            float f[LPL], b[LPL];
+            f[0] = v[0];
+#pragma unroll
+            for (int i = 1; i < LPL; ++i) f[i] = fminf(v[i], f[i - 1] + wt);
+            b[LPL - 1] = v[LPL - 1];
+#pragma unroll
+            for (int i = LPL - 2; i >= 0; --i) b[i] = fminf(v[i], b[i + 1] + wt);
+            for (int s = 0; s < dt_steps; ++s) {
+                const float cl = from_left(f[LPL - 1], dl);
+                const float cr = from_right(b[0], dr);
+#pragma unroll
+                for (int i = 0; i < LPL; ++i) {
+                    f[i] = fminf(f[i], wdist(wt, i + 1, cl));
+                    b[i] = fminf(b[i], wdist(wt, LPL - i, cr));
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < LPL; ++i) e[i] = fminf(f[i], b[i]);
+            return;
+        }
+        constexpr bool T3 = MF == 3;
         const float w1 = (T3 || T > 1) ? wt : kBig;
         const float w2 = T > 2 ? wt + wt : kBig;
         const float l1 = from_left(v[LPL - 1], dl);
@@ -622,14 +647,14 @@ struct PipeStore {
     }
 };
 
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, bool T3, int MG>
-__global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
-    __shared__ __attribute__((aligned(16))) uint32_t lds[pipe_lds_words(LPL, HAS_THETA)];
+// All passes of one mode group for the chains chain0 .. chain0 + 64 / G - 1 of a, by the three
+// waves of a workgroup.
+template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+__device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_t* lds) {
     constexpr int C = pipe_chunk(LPL);
-    constexpr int CPW = 64 / G;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
     const int lane = (int)threadIdx.x % 64;
-    const int sub = lane % G, chain = (int)blockIdx.x * CPW + lane / G;
+    const int sub = lane % G, chain = chain0 + lane / G;
     const int n_chunks = (a.n + C - 1) / C;
     lds_u32* const base = (lds_u32*)lds;
     lds_u32* const obase = base + pipe_in_lds(LPL, HAS_THETA);
@@ -645,13 +670,15 @@ __global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
         return g;
     };
     if (wave == 0) {
-        PipeChain<G, LPL, T3, HAS_THETA> ch;
+        PipeChain<G, LPL, MF, HAS_THETA> ch;
         ch.in.base = base;
         ch.out.base = obase;
         ch.wgt = wbase + (lane - sub);
         ch.lane = lane;
         ch.sub = sub;
         ch.T = a.T;
+        const int need = (a.T - 1 + LPL - 1) / LPL;
+        ch.dt_steps = need < G - 1 ? need : G - 1;
 #pragma unroll
         for (int i = 0; i < LPL; ++i) ch.lv[i] = FULL || (chain < a.n_chains && sub * LPL + i < a.K);
         ch.template pass<0>(n_chunks, 0.0f);
@@ -717,40 +744,47 @@ __global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
     }
 }
 
-// Half-steps (mode kModeIterative or kModeNaive), the final pass and the column optimum
-// pass of args, for K <= G * LPL labels and T <= 3.
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+__global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[pipe_lds_words(LPL, HAS_THETA)];
+    pipe_run<G, LPL, TT, FULL, HAS_THETA, MF, MG>(a, (int)blockIdx.x * (64 / G), lds);
+}
+
+// The kernels of a tile: half-steps (mode kModeIterative or kModeNaive), the final pass and
+// the column optimum pass, for K <= G * LPL labels.  SCAN: messages by scans (any T), else
+// the direct window (T <= 3).
+template <int G, int LPL, bool SCAN, typename TT, bool FULL, bool HAS_THETA>
 hipError_t launch_pipe_full(const SweepArgs& a, hipStream_t st) {
     constexpr int CPW = 64 / G;
     const dim3 grid((unsigned)((a.n_chains + CPW - 1) / CPW)), block(192);
-#define DM_PIPE(T3, MG) hipLaunchKernelGGL((pipe_kernel<G, LPL, TT, FULL, HAS_THETA, T3, MG>), grid, block, 0, st, a)
+#define DM_PIPE(MF, MG) hipLaunchKernelGGL((pipe_kernel<G, LPL, TT, FULL, HAS_THETA, MF, MG>), grid, block, 0, st, a)
     if (a.mode == kModeFinal) {
-        DM_PIPE(false, kGroupFinal);
+        DM_PIPE(SCAN ? 0 : 2, kGroupFinal);
     } else if (a.mode == kModeOptimum) {
-        if constexpr (!HAS_THETA) DM_PIPE(false, kGroupOptimum);
+        if constexpr (!HAS_THETA) DM_PIPE(SCAN ? 0 : 2, kGroupOptimum);
         else return hipErrorInvalidValue;
-    } else if (a.T == 3) {
-        DM_PIPE(true, kGroupHalfStep);
+    } else if (SCAN || a.T == 3) {
+        DM_PIPE(SCAN ? 0 : 3, kGroupHalfStep);
     } else {
-        DM_PIPE(false, kGroupHalfStep);
+        DM_PIPE(SCAN ? 0 : 2, kGroupHalfStep);
     }
 #undef DM_PIPE
     return hipGetLastError();
 }
 
-template <int G, int LPL, typename TT, bool HAS_THETA>
+template <int G, int LPL, bool SCAN, typename TT, bool HAS_THETA>
 hipError_t launch_pipe_tt(const SweepArgs& a, hipStream_t st) {
     // one label per lane: a full tile saves nothing
     if constexpr (LPL > 1)
-        if (a.K == G * LPL) return launch_pipe_full<G, LPL, TT, true, HAS_THETA>(a, st);
-    return launch_pipe_full<G, LPL, TT, false, HAS_THETA>(a, st);
+        if (a.K == G * LPL) return launch_pipe_full<G, LPL, SCAN, TT, true, HAS_THETA>(a, st);
+    return launch_pipe_full<G, LPL, SCAN, TT, false, HAS_THETA>(a, st);
 }
 
-template <int G, int LPL>
+template <int G, int LPL, bool SCAN>
 hipError_t launch_pipe(const SweepArgs& a, dm_dtype dt, hipStream_t st) {
-    if (a.theta == nullptr) return launch_pipe_tt<G, LPL, float, false>(a, st);
-    if (dt == DM_F16) return launch_pipe_tt<G, LPL, _Float16, true>(a, st);
-    return launch_pipe_tt<G, LPL, float, true>(a, st);
+    if (a.theta == nullptr) return launch_pipe_tt<G, LPL, SCAN, float, false>(a, st);
+    if (dt == DM_F16) return launch_pipe_tt<G, LPL, SCAN, _Float16, true>(a, st);
+    return launch_pipe_tt<G, LPL, SCAN, float, true>(a, st);
 }
 
 }  // namespace dm

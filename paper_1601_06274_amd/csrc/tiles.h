@@ -16,7 +16,17 @@
     X(64, 3)                \
     X(64, 4)
 
-// Tiles of the pipelined sweeps (dmm_pipe.h), chosen by the library alone.
+// Tiles of the pipelined sweeps (dmm_pipe.h), chosen by the library alone: with direct
+// window messages, and (the chain tiles that a call may use, as results round by tile) with
+// scan messages.
+#define DM_FOR_EACH_PIPE_SCAN(Z) \
+    Z(8, 4)                      \
+    Z(16, 4)                     \
+    Z(32, 3)                     \
+    Z(32, 4)                     \
+    Z(64, 3)                     \
+    Z(64, 4)
+
 #define DM_FOR_EACH_PIPE(Y) \
     Y(16, 1)               \
     Y(32, 1)               \
@@ -24,3 +34,14 @@
     Y(64, 2)               \
     Y(64, 3)               \
     Y(64, 4)
+
+namespace dm {
+
+struct Tile {
+    int G, LPL;
+};
+
+// Tile of the pipelined sweeps with direct window messages: the fewest labels per lane.
+inline Tile window_tile(int K) { return K <= 16 ? Tile{16, 1} : (K <= 32 ? Tile{32, 1} : Tile{64, (K + 63) / 64}); }
+
+}  // namespace dm

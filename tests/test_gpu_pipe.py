@@ -5,9 +5,15 @@ chains for several workgroups to share a CU."""
 import pytest
 import torch
 
-import synth
-
 pytestmark = pytest.mark.gpu
+
+
+def _instance(H, W, K, dtype, seed):
+    g = torch.Generator().manual_seed(seed)
+    # quarter steps: exact ties between candidates and between labels are frequent
+    cost = (torch.randint(0, 5, (H, W, K), generator=g) / 4).to(dtype).cuda()
+    w_h, w_v = (torch.rand(s, generator=g).cuda() * 0.5 for s in ((H, W - 1), (H - 1, W)))
+    return cost, w_h, w_v
 
 
 def _compare(H, W, K, T, dtype, minorant="iterative", half=0, seed=0, gammas=(0.25, 0.25, 1.0)):
@@ -57,3 +63,25 @@ def test_many_chains(K):
     """Two and more workgroups per CU (rows and columns)."""
     _compare(600, 61, K, 3, torch.float16, seed=K)
     _compare(61, 600, K, 3, torch.float32, seed=K + 1)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
+@pytest.mark.parametrize("T", [4, 6, 9, 40])
+@pytest.mark.parametrize("K", [17, 30, 32, 50, 64, 90, 96, 100, 126, 128, 150, 192, 212, 256])
+def test_scans(K, T, dtype):
+    from paper_1601_06274_amd import ops
+    for H, W in ((13, 22), (530, 9)) if T == 6 else ((7, 11),):
+        print(f"[case] {H}x{W}x{K} T={T} {dtype}", flush=True)
+        cost, w_h, w_v = _instance(H, W, K, dtype, K + T)
+        kw = dict(T=T, n_iters=2, tile=ops.tile_for(K))
+        plan = ops.BatchedPlan([dict(cost=cost, w_h=w_h, w_v=w_v)], want_minmarg=True, **kw)
+        try:
+            plan.run()
+            r = ops.solve_discrete(cost, w_h, w_v, **kw)
+            torch.cuda.synchronize()
+            ref = plan.instances[0]
+            for name in ("dual", "minmarg", "labels"):
+                assert torch.equal(getattr(r, name), ref[name]), f"{name} differs"
+            assert r.bounds[0].item() == ref["bounds"][0].item()
+        finally:
+            plan.close()
