@@ -23,6 +23,12 @@ namespace dm {
     extern template hipError_t launch_batched_tile<g, l>(const BatchLaunch&, bool, dm_dtype, int, hipStream_t);
 DM_FOR_EACH_TILE(DM_EXTERN_BTILE)
 #undef DM_EXTERN_BTILE
+template <int G, int LPL>
+hipError_t launch_batched_pipe(const BatchLaunch&, bool, dm_dtype, hipStream_t);
+#define DM_EXTERN_BPIPE(g, l) \
+    extern template hipError_t launch_batched_pipe<g, l>(const BatchLaunch&, bool, dm_dtype, hipStream_t);
+DM_FOR_EACH_PIPE(DM_EXTERN_BPIPE)
+#undef DM_EXTERN_BPIPE
 
 namespace {
 
@@ -33,6 +39,18 @@ hipError_t launch_batched(int G, int LPL, const BatchLaunch& bl, bool full, dm_d
 #undef DM_BCASE
     return hipErrorInvalidValue;
 }
+
+hipError_t launch_pipe_class(int G, int LPL, const BatchLaunch& bl, bool full, dm_dtype dt, hipStream_t st) {
+#define DM_BCASE(g, l) \
+    if (G == g && LPL == l) return launch_batched_pipe<g, l>(bl, full, dt, st);
+    DM_FOR_EACH_PIPE(DM_BCASE)
+#undef DM_BCASE
+    return hipErrorInvalidValue;
+}
+
+// Direct window messages (T <= 3) on every chain tile that holds K labels: the pipelined
+// sweeps give those tiles' results bit for bit.
+bool pipe_serves(int K, int T, int tile_lpl) { return T <= 3 && (tile_lpl != 0 ? T - 1 <= tile_lpl : K > 4); }
 
 __global__ void zero_i32_kernel(int* __restrict__ p, long long n) {
     for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x)
@@ -119,7 +137,7 @@ constexpr int kBatchEnergyBlocks = 32;  // energy partial sums per instance
 
 struct Class {
     int family, G, LPL;
-    bool full;
+    bool full, pipe;  // pipe: a pipelined sweep's tile, a workgroup per item
     std::vector<BatchItem> items;
     BatchItem* d_items = nullptr;
 };
@@ -199,6 +217,7 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
                 big = j;
         dm_discrete_params q = *p;
         q.keep_checkpoints = 0;
+        if (p->tile_lanes == 0 && pipe_serves(K, p->trunc_T, 0)) continue;  // no chain tile needed
         if (p->tile_lanes == 0) {
             q.tile_lanes = q.labels_per_lane = q.tile_lanes_v = q.labels_per_lane_v = 0;
             const int st = dm_autotune_tiles(inst[big].s, cost_dtype, &q, nullptr);
@@ -267,12 +286,19 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
     if (e != hipSuccess) return fail("copy instance table", e);
 
     // 3. classes (family, tile, full) with their work items, longest chains first
-    std::map<std::tuple<int, int, int, int>, int> class_of;
+    std::map<std::tuple<int, int, int, int, int>, int> class_of;
     for (int fam = 0; fam < 2; ++fam) {
         for (int i = 0; i < n; ++i) {
-            const auto t = fam == 0 ? tile_of_k[inst[i].s.K].first : tile_of_k[inst[i].s.K].second;
-            const bool full = t.first * t.second == inst[i].s.K;
-            const auto key = std::make_tuple(fam, t.first, t.second, full ? 1 : 0);
+            const int K = inst[i].s.K;
+            std::pair<int, int> t{0, 0};
+            if (tile_of_k.count(K)) t = fam == 0 ? tile_of_k[K].first : tile_of_k[K].second;
+            const bool pipe = pipe_serves(K, p->trunc_T, t.second);
+            if (pipe) {
+                const Tile w = window_tile(K);
+                t = {w.G, w.LPL};
+            }
+            const bool full = t.first * t.second == K;
+            const auto key = std::make_tuple(fam, t.first, t.second, full ? 1 : 0, pipe ? 1 : 0);
             if (!class_of.count(key)) {
                 class_of[key] = (int)plan->classes.size();
                 Class c;
@@ -280,6 +306,7 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
                 c.G = t.first;
                 c.LPL = t.second;
                 c.full = full;
+                c.pipe = pipe;
                 plan->classes.push_back(c);
             }
             Class& c = plan->classes[class_of[key]];
@@ -423,7 +450,8 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
             bl.n_pass = p->max_pass;
             for (int g = 0; g < 8; ++g) bl.gamma[g] = p->gamma[g];
             const int workers = std::max(1, std::min(bl.n_items, n_cu * 8));
-            note(launch_batched(c.G, c.LPL, bl, c.full, cost_dtype, workers, s2));
+            note(c.pipe ? launch_pipe_class(c.G, c.LPL, bl, c.full, cost_dtype, s2)
+                        : launch_batched(c.G, c.LPL, bl, c.full, cost_dtype, workers, s2));
             ++used;
         }
         for (int u = 0; u < std::min(used, kSide); ++u) {

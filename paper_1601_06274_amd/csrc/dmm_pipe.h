@@ -26,11 +26,14 @@
 // (6.3 TB/s), 1242x375, K = 192, FP16 rows 1130 -> 1074 us.  The chain wave alone takes 72,
 // 106, 128 ns a node at 1, 2, 3 labels per lane.  Messages by scans (T > 3), whole solve of
 // 611x437, K = 100, T = 6: 5.91 -> 5.10 ms.
+// A batched plan (a workgroup per chains of every frame, longest first), four iterations of 64
+// uneven frames: 177 -> 164 ms.
 //
 // The arithmetic of every value is chain_kernel's, operation for operation, so the results
 // are the same bit for bit, whatever tile (lanes, labels per lane) either uses.
 #pragma once
 
+#include "batched_kernels.h"
 #include "dmm_kernels.h"
 
 namespace dm {
@@ -750,6 +753,15 @@ __global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
     pipe_run<G, LPL, TT, FULL, HAS_THETA, MF, MG>(a, (int)blockIdx.x * (64 / G), lds);
 }
 
+// One workgroup per work item of a batched plan's table (longest chains first).
+template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+__global__ __launch_bounds__(192) void batched_pipe_kernel(BatchLaunch bl) {
+    __shared__ __attribute__((aligned(16))) uint32_t lds[pipe_lds_words(LPL, HAS_THETA)];
+    const BatchItem bi = bl.items[blockIdx.x];
+    const SweepArgs a = batch_args(bl.insts[bi.inst], bl);
+    pipe_run<G, LPL, TT, FULL, HAS_THETA, MF, MG>(a, bi.chain, lds);
+}
+
 // The kernels of a tile: half-steps (mode kModeIterative or kModeNaive), the final pass and
 // the column optimum pass, for K <= G * LPL labels.  SCAN: messages by scans (any T), else
 // the direct window (T <= 3).
@@ -785,6 +797,41 @@ hipError_t launch_pipe(const SweepArgs& a, dm_dtype dt, hipStream_t st) {
     if (a.theta == nullptr) return launch_pipe_tt<G, LPL, SCAN, float, false>(a, st);
     if (dt == DM_F16) return launch_pipe_tt<G, LPL, SCAN, _Float16, true>(a, st);
     return launch_pipe_tt<G, LPL, SCAN, float, true>(a, st);
+}
+
+// Batched form (direct window): family 0 reads the cost, full: K == G * LPL.
+template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+hipError_t launch_batched_pipe_full(const BatchLaunch& bl, hipStream_t st) {
+#define DM_BPIPE(MF, MG)                                                                                        \
+    hipLaunchKernelGGL((batched_pipe_kernel<G, LPL, TT, FULL, HAS_THETA, MF, MG>), dim3((unsigned)bl.n_items), \
+                       dim3(192), 0, st, bl)
+    if (bl.mode == kModeFinal) {
+        if constexpr (HAS_THETA) DM_BPIPE(2, kGroupFinal);
+        else return hipErrorInvalidValue;
+    } else if (bl.mode == kModeOptimum) {
+        if constexpr (!HAS_THETA) DM_BPIPE(2, kGroupOptimum);
+        else return hipErrorInvalidValue;
+    } else if (bl.T == 3) {
+        DM_BPIPE(3, kGroupHalfStep);
+    } else {
+        DM_BPIPE(2, kGroupHalfStep);
+    }
+#undef DM_BPIPE
+    return hipGetLastError();
+}
+
+template <int G, int LPL, typename TT, bool HAS_THETA>
+hipError_t launch_batched_pipe_tt(const BatchLaunch& bl, bool full, hipStream_t st) {
+    if constexpr (LPL > 1)
+        if (full) return launch_batched_pipe_full<G, LPL, TT, true, HAS_THETA>(bl, st);
+    return launch_batched_pipe_full<G, LPL, TT, false, HAS_THETA>(bl, st);
+}
+
+template <int G, int LPL>
+hipError_t launch_batched_pipe(const BatchLaunch& bl, bool full, dm_dtype dt, hipStream_t st) {
+    if (bl.family != 0) return launch_batched_pipe_tt<G, LPL, float, false>(bl, full, st);
+    if (dt == DM_F16) return launch_batched_pipe_tt<G, LPL, _Float16, true>(bl, full, st);
+    return launch_batched_pipe_tt<G, LPL, float, true>(bl, full, st);
 }
 
 }  // namespace dm
