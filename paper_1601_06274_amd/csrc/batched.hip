@@ -297,7 +297,9 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
                 const Tile w = window_tile(K);
                 t = {w.G, w.LPL};
             }
-            const bool full = t.first * t.second == K;
+            // one-wave tiles: all labels exist; pipelined ones: a lane's labels all do or none
+            const bool full = pipe ? K % t.second == 0 && (fam != 0 || cost_dtype == DM_F32 || K % 2 == 0)
+                                   : t.first * t.second == K;
             const auto key = std::make_tuple(fam, t.first, t.second, full ? 1 : 0, pipe ? 1 : 0);
             if (!class_of.count(key)) {
                 class_of[key] = (int)plan->classes.size();

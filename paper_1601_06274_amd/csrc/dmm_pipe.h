@@ -28,6 +28,9 @@
 // 611x437, K = 100, T = 6: 5.91 -> 5.10 ms.
 // A batched plan (a workgroup per chains of every frame, longest first), four iterations of 64
 // uneven frames: 177 -> 164 ms.
+// Whole-lane vectors where K is a multiple of the labels per lane, not only for a full tile
+// (one access a label before): the T = 6 solve above 5.10 -> 4.30 ms, a plan of six
+// frames up to 640x360, K = 128, with refinement 11.0 -> 10.1 ms.
 //
 // The arithmetic of every value is chain_kernel's, operation for operation, so the results
 // are the same bit for bit, whatever tile (lanes, labels per lane) either uses.
@@ -309,12 +312,18 @@ struct PipeChain {
 };
 
 // ------------------------------------------------------------------ loader
+// VEC: every lane's labels exist or none do (K is a multiple of the labels per lane), so a
+// lane's values move as one vector; else one access per label.
+template <int LPL, typename TT, bool HAS_THETA>
+bool pipe_vec(int K) {
+    return K % LPL == 0 && !(HAS_THETA && sizeof(TT) == 2 && K % 2 != 0);  // FP16 costs are read as dwords
+}
 // Node offsets: a lane's offset in a volume is fixed (its label at node 0; out of range for
 // labels and chains that do not exist), the node's offset is scalar and stays inside the
 // chain.  Nodes beyond the end are loaded at an out-of-range lane offset: no access, as the
 // chain's last nodes are stored by another wave while such a load could be in flight, and
 // the next pass's load of the same line could be given what it brought.
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA>
 struct PipeLane {
     static constexpr int ES = (int)sizeof(TT);
     unsigned f0, th0, w0, lab0;       // byte offsets at node 0: FP32 volumes, cost, edge weights, labels
@@ -327,8 +336,9 @@ struct PipeLane {
         const unsigned long long cpx = (unsigned long long)(ok ? chain : 0) * (unsigned long long)a.chain_px;
         const unsigned long long e0 = cpx * (unsigned long long)a.K + (unsigned long long)(sub * LPL);
         const unsigned nk = (unsigned)(a.node_px * (long long)a.K);
-        f0 = ok ? (unsigned)(e0 * 4ull) : kOOB;
-        th0 = ok ? (unsigned)(e0 * (unsigned long long)ES) : kOOB;
+        const bool any = ok && sub * LPL < K;
+        f0 = any ? (unsigned)(e0 * 4ull) : kOOB;
+        th0 = any ? (unsigned)(e0 * (unsigned long long)ES) : kOOB;
         w0 = ok ? (unsigned)((unsigned long long)chain * (unsigned long long)a.w_chain * 4ull) : kOOB;
         lab0 = ok && sub == 0 ? (unsigned)(cpx * 4ull) : kOOB;
         f_step = nk * 4u;
@@ -337,7 +347,7 @@ struct PipeLane {
         lab_step = (unsigned)(a.node_px * 4);
 #pragma unroll
         for (int i = 0; i < LPL; ++i) {
-            lv[i] = ok && (FULL || sub * LPL + i < K);
+            lv[i] = ok && sub * LPL + i < K;
             f[i] = lv[i] ? f0 + 4u * i : kOOB;
             th[i] = lv[i] ? th0 + (unsigned)(ES * i) : kOOB;
         }
@@ -360,17 +370,17 @@ __device__ __forceinline__ void load_words_s(__amdgpu_buffer_rsrc_t r, unsigned 
         w[0] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, (int)so, 0);
     }
 }
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA>
 struct PipeLoad {
     static constexpr int C = pipe_chunk(LPL);
     static constexpr int NIN = pipe_in_words(LPL, HAS_THETA);
     static constexpr int D = pipe_ahead(LPL, HAS_THETA), U = D / C;  // nodes in flight, intervals per turn of the ring
-    // FP16 costs of a full tile: a lane's labels packed in dwords; 3 labels start at 6 * sub
+    // FP16 costs moved as vectors: a lane's labels packed in dwords; 3 labels start at 6 * sub
     // bytes, so the 8 bytes from the dword at or below hold them, shifted by a half for odd
-    // lanes (the tile's labels end on a dword).
-    static constexpr bool kPacked = sizeof(TT) == 2 && FULL && LPL > 1;
+    // lanes (the labels of a pixel end on a dword).
+    static constexpr bool kPacked = sizeof(TT) == 2 && VEC && LPL > 1;
     static constexpr int TW = sizeof(TT) == 2 ? (kPacked ? (LPL + 1) / 2 : LPL) : LPL;
-    using Lane = PipeLane<G, LPL, TT, FULL, HAS_THETA>;
+    using Lane = PipeLane<G, LPL, TT, VEC, HAS_THETA>;
     struct Node {
         uint32_t th[TW], lam[LPL], rev[LPL];
     };
@@ -382,7 +392,7 @@ struct PipeLoad {
 
     __device__ __forceinline__ static void load_f32(const Lane& ln, __amdgpu_buffer_rsrc_t r, bool live, unsigned so,
                                                     uint32_t* w) {
-        if constexpr (FULL) {
+        if constexpr (VEC) {
             load_words_s<LPL>(r, live ? ln.f0 : kOOB, so, w);
         } else {
 #pragma unroll
@@ -424,8 +434,8 @@ struct PipeLoad {
                 for (int i = 0; i < LPL; ++i)
                     nd.th[i] = __builtin_amdgcn_raw_buffer_load_b16(r_theta, (int)(live ? ln.th[i] : kOOB), (int)st, 0);
             } else if constexpr (kPacked) {
-                load_words_s<TW>(r_theta, live && ln.ok ? ln.th0 & ~3u : kOOB, st, nd.th);
-            } else if constexpr (FULL) {
+                load_words_s<TW>(r_theta, live ? ln.th0 & ~3u : kOOB, st, nd.th);
+            } else if constexpr (VEC) {
                 load_words_s<LPL>(r_theta, live ? ln.th0 : kOOB, st, nd.th);
             } else {
 #pragma unroll
@@ -471,7 +481,7 @@ struct PipeLoad {
                 for (int l = 0; l < LPL; ++l) {
                     const float lam = __builtin_bit_cast(float, nd.lam[l]);
                     const float x = HAS_THETA ? __builtin_fmaf(cost(ln, nd, l), one, -lam) : lam;
-                    w[l] = __builtin_bit_cast(uint32_t, (FULL || ln.lv[l]) ? x : kBig);
+                    w[l] = __builtin_bit_cast(uint32_t, ln.lv[l] ? x : kBig);
                     w[2 * LPL + l] = nd.lam[l];
                     if constexpr (REV) w[LPL + l] = has_next ? nd.rev[l] : 0u;  // no message beyond the end
                 }
@@ -511,11 +521,11 @@ struct PipeLoad {
 };
 
 // ------------------------------------------------------------------ storer
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA>
 struct PipeStore {
     static constexpr int C = pipe_chunk(LPL);
     static constexpr int NIN = pipe_in_words(LPL, HAS_THETA), NOUT = pipe_out_words(LPL);
-    using Lane = PipeLane<G, LPL, TT, FULL, HAS_THETA>;
+    using Lane = PipeLane<G, LPL, TT, VEC, HAS_THETA>;
     PipeRec<NIN, kPipeBufs * C> in;
     PipeRec<NOUT, 2 * C> out;
     int lane, n;
@@ -530,7 +540,7 @@ struct PipeStore {
         unsigned os[LPL];
 #pragma unroll
         for (int i = 0; i < LPL; ++i) os[i] = ln.lv[i] ? ln.f[i] + so : kOOB;
-        store_f32<LPL, FULL>(r, ln.ok ? ln.f0 + so : kOOB, os, x);
+        store_f32<LPL, VEC>(r, ln.f0 != kOOB ? ln.f0 + so : kOOB, os, x);
     }
 
     // Group minima of N nodes' lane minima x.  A whole wave's four at a time: two permlane
@@ -601,7 +611,7 @@ struct PipeStore {
                     for (int l = LPL - 1; l >= 0; --l) {
                         const float m = __builtin_bit_cast(float, o[i][l]);
                         x[l] = m - mn[i];
-                        if ((FULL || ln.lv[l]) && m == mn[i]) first = ln.sub * LPL + l;
+                        if (ln.lv[l] && m == mn[i]) first = ln.sub * LPL + l;
                     }
                     int lab = group_min_i<G>(first);
                     lab = lab < ln.K ? lab : ln.K - 1;  // a label always exists for finite costs
@@ -652,7 +662,7 @@ struct PipeStore {
 
 // All passes of one mode group for the chains chain0 .. chain0 + 64 / G - 1 of a, by the three
 // waves of a workgroup.
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA, int MF, int MG>
 __device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_t* lds) {
     constexpr int C = pipe_chunk(LPL);
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / 64);
@@ -683,7 +693,7 @@ __device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_
         const int need = (a.T - 1 + LPL - 1) / LPL;
         ch.dt_steps = need < G - 1 ? need : G - 1;
 #pragma unroll
-        for (int i = 0; i < LPL; ++i) ch.lv[i] = FULL || (chain < a.n_chains && sub * LPL + i < a.K);
+        for (int i = 0; i < LPL; ++i) ch.lv[i] = chain < a.n_chains && sub * LPL + i < a.K;
         ch.template pass<0>(n_chunks, 0.0f);
         if constexpr (MG == kGroupFinal) {
             ch.template pass<3>(n_chunks, 0.0f);
@@ -694,7 +704,7 @@ __device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_
                 ch.template pass<2>(n_chunks, 0.0f);
         }
     } else if (wave == 1) {
-        using LD = PipeLoad<G, LPL, TT, FULL, HAS_THETA>;
+        using LD = PipeLoad<G, LPL, TT, VEC, HAS_THETA>;
         const typename LD::Lane ln(a, chain, sub);
         LD ld;
         ld.in.base = base;
@@ -717,7 +727,7 @@ __device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_
             }
         }
     } else {
-        using ST = PipeStore<G, LPL, TT, FULL, HAS_THETA>;
+        using ST = PipeStore<G, LPL, TT, VEC, HAS_THETA>;
         const typename ST::Lane ln(a, chain, sub);
         ST sr;
         sr.in.base = base;
@@ -747,29 +757,29 @@ __device__ __forceinline__ void pipe_run(const SweepArgs& a, int chain0, uint32_
     }
 }
 
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA, int MF, int MG>
 __global__ __launch_bounds__(192) void pipe_kernel(SweepArgs a) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[pipe_lds_words(LPL, HAS_THETA)];
-    pipe_run<G, LPL, TT, FULL, HAS_THETA, MF, MG>(a, (int)blockIdx.x * (64 / G), lds);
+    pipe_run<G, LPL, TT, VEC, HAS_THETA, MF, MG>(a, (int)blockIdx.x * (64 / G), lds);
 }
 
 // One workgroup per work item of a batched plan's table (longest chains first).
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA, int MF, int MG>
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA, int MF, int MG>
 __global__ __launch_bounds__(192) void batched_pipe_kernel(BatchLaunch bl) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[pipe_lds_words(LPL, HAS_THETA)];
     const BatchItem bi = bl.items[blockIdx.x];
     const SweepArgs a = batch_args(bl.insts[bi.inst], bl);
-    pipe_run<G, LPL, TT, FULL, HAS_THETA, MF, MG>(a, bi.chain, lds);
+    pipe_run<G, LPL, TT, VEC, HAS_THETA, MF, MG>(a, bi.chain, lds);
 }
 
 // The kernels of a tile: half-steps (mode kModeIterative or kModeNaive), the final pass and
 // the column optimum pass, for K <= G * LPL labels.  SCAN: messages by scans (any T), else
 // the direct window (T <= 3).
-template <int G, int LPL, bool SCAN, typename TT, bool FULL, bool HAS_THETA>
+template <int G, int LPL, bool SCAN, typename TT, bool VEC, bool HAS_THETA>
 hipError_t launch_pipe_full(const SweepArgs& a, hipStream_t st) {
     constexpr int CPW = 64 / G;
     const dim3 grid((unsigned)((a.n_chains + CPW - 1) / CPW)), block(192);
-#define DM_PIPE(MF, MG) hipLaunchKernelGGL((pipe_kernel<G, LPL, TT, FULL, HAS_THETA, MF, MG>), grid, block, 0, st, a)
+#define DM_PIPE(MF, MG) hipLaunchKernelGGL((pipe_kernel<G, LPL, TT, VEC, HAS_THETA, MF, MG>), grid, block, 0, st, a)
     if (a.mode == kModeFinal) {
         DM_PIPE(SCAN ? 0 : 2, kGroupFinal);
     } else if (a.mode == kModeOptimum) {
@@ -786,10 +796,9 @@ hipError_t launch_pipe_full(const SweepArgs& a, hipStream_t st) {
 
 template <int G, int LPL, bool SCAN, typename TT, bool HAS_THETA>
 hipError_t launch_pipe_tt(const SweepArgs& a, hipStream_t st) {
-    // one label per lane: a full tile saves nothing
     if constexpr (LPL > 1)
-        if (a.K == G * LPL) return launch_pipe_full<G, LPL, SCAN, TT, true, HAS_THETA>(a, st);
-    return launch_pipe_full<G, LPL, SCAN, TT, false, HAS_THETA>(a, st);
+        if (!pipe_vec<LPL, TT, HAS_THETA>(a.K)) return launch_pipe_full<G, LPL, SCAN, TT, false, HAS_THETA>(a, st);
+    return launch_pipe_full<G, LPL, SCAN, TT, true, HAS_THETA>(a, st);
 }
 
 template <int G, int LPL, bool SCAN>
@@ -799,11 +808,11 @@ hipError_t launch_pipe(const SweepArgs& a, dm_dtype dt, hipStream_t st) {
     return launch_pipe_tt<G, LPL, SCAN, float, true>(a, st);
 }
 
-// Batched form (direct window): family 0 reads the cost, full: K == G * LPL.
-template <int G, int LPL, typename TT, bool FULL, bool HAS_THETA>
+// Batched form (direct window): family 0 reads the cost; vec: see pipe_vec.
+template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA>
 hipError_t launch_batched_pipe_full(const BatchLaunch& bl, hipStream_t st) {
 #define DM_BPIPE(MF, MG)                                                                                        \
-    hipLaunchKernelGGL((batched_pipe_kernel<G, LPL, TT, FULL, HAS_THETA, MF, MG>), dim3((unsigned)bl.n_items), \
+    hipLaunchKernelGGL((batched_pipe_kernel<G, LPL, TT, VEC, HAS_THETA, MF, MG>), dim3((unsigned)bl.n_items), \
                        dim3(192), 0, st, bl)
     if (bl.mode == kModeFinal) {
         if constexpr (HAS_THETA) DM_BPIPE(2, kGroupFinal);
@@ -821,17 +830,17 @@ hipError_t launch_batched_pipe_full(const BatchLaunch& bl, hipStream_t st) {
 }
 
 template <int G, int LPL, typename TT, bool HAS_THETA>
-hipError_t launch_batched_pipe_tt(const BatchLaunch& bl, bool full, hipStream_t st) {
+hipError_t launch_batched_pipe_tt(const BatchLaunch& bl, bool vec, hipStream_t st) {
     if constexpr (LPL > 1)
-        if (full) return launch_batched_pipe_full<G, LPL, TT, true, HAS_THETA>(bl, st);
-    return launch_batched_pipe_full<G, LPL, TT, false, HAS_THETA>(bl, st);
+        if (!vec) return launch_batched_pipe_full<G, LPL, TT, false, HAS_THETA>(bl, st);
+    return launch_batched_pipe_full<G, LPL, TT, true, HAS_THETA>(bl, st);
 }
 
 template <int G, int LPL>
-hipError_t launch_batched_pipe(const BatchLaunch& bl, bool full, dm_dtype dt, hipStream_t st) {
-    if (bl.family != 0) return launch_batched_pipe_tt<G, LPL, float, false>(bl, full, st);
-    if (dt == DM_F16) return launch_batched_pipe_tt<G, LPL, _Float16, true>(bl, full, st);
-    return launch_batched_pipe_tt<G, LPL, float, true>(bl, full, st);
+hipError_t launch_batched_pipe(const BatchLaunch& bl, bool vec, dm_dtype dt, hipStream_t st) {
+    if (bl.family != 0) return launch_batched_pipe_tt<G, LPL, float, false>(bl, vec, st);
+    if (dt == DM_F16) return launch_batched_pipe_tt<G, LPL, _Float16, true>(bl, vec, st);
+    return launch_batched_pipe_tt<G, LPL, float, true>(bl, vec, st);
 }
 
 }  // namespace dm

@@ -60,7 +60,7 @@ def _compare(H, W, K, T, dtype, minorant="iterative", half=0, seed=0, gammas=(0.
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16])
-@pytest.mark.parametrize("K", [5, 16, 17, 32, 33, 63, 64, 65, 66, 127, 128, 129, 191, 192, 193, 255, 256])
+@pytest.mark.parametrize("K", [5, 16, 17, 32, 33, 63, 64, 65, 66, 72, 100, 127, 128, 129, 130, 132, 191, 192, 193, 196, 255, 256])
 def test_label_counts(K, dtype):
     _compare(13, 22, K, 3, dtype, seed=K)
 
