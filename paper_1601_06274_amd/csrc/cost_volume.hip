@@ -6,15 +6,69 @@
 // (Sec. 3.1); this kernel provides a truncated windowed SAD in the same role.
 // Edge strengths are image dependent, lower across image edges (Sec. 2.1).
 //
-// Layout: the volume is label-major ([y][x][d], d fastest).  Windows up to 7 are computed
-// on strips of rows (sad_strip.h).  Border handling: window positions are clamped to the
+// Layout: the volume is label-major ([y][x][d], d fastest).  Small windows of large
+// frames are computed on strips of rows (sad_strip.h), others a row at a time.  Border handling: window positions are clamped to the
 // image (clamp-to-edge), and a right-image column left of 0 costs `trunc`.
 #include "common.h"
 #include "sad_strip.h"
 
 namespace dm {
 
-// Any odd window (the strips cover radii 0..3): one thread per (pixel, label).
+// Small frames and wide windows: a block owns one row and kSadTX pixels, its threads are the
+// labels (K <= 256 -> 1..4 waves), so each pixel's K costs are one coalesced write.  Each
+// thread sums the window vertically for the TX + 2R window columns of its label, then slides
+// the horizontal sum: the same sums in the same order as the strips'.
+constexpr int kSadTX = 16;  // pixels per block
+
+template <typename OT, int R>
+__global__ __launch_bounds__(256) void sad_tile_kernel(const float* __restrict__ IL, const float* __restrict__ IR, int W,
+                                                       int H, int K, float trunc, float inv_area,
+                                                       OT* __restrict__ out) {
+    constexpr int TX = kSadTX;
+    constexpr int NR = 2 * R + 1;   // window rows
+    constexpr int NC = TX + 2 * R;  // window columns of the tile
+    __shared__ float sL[NR][NC];
+    __shared__ float sR[NR][NC + 255];
+    const int y = blockIdx.y;
+    const int x0 = blockIdx.x * TX;
+    const int lr = x0 - R;            // image column of sL[.][0]
+    const int rr = x0 - R - (K - 1);  // image column of sR[.][0]
+    const int nrc = NC + K - 1;
+    for (int e = threadIdx.x; e < NR * nrc; e += blockDim.x) {
+        const int row = e / nrc, j = e - row * nrc;
+        const int yy = min(max(y + row - R, 0), H - 1);
+        const int xc = rr + j;
+        sR[row][j] = (xc >= 0 && xc < W) ? IR[(long long)yy * W + xc] : 0.0f;
+        if (j < NC) sL[row][j] = IL[(long long)yy * W + min(max(lr + j, 0), W - 1)];
+    }
+    __syncthreads();
+    const int d = threadIdx.x;
+    if (d >= K) return;
+    // vertical window sums at the (clamped) columns lr + i
+    float col[NC];
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+        const int xx = min(max(lr + i, 0), W - 1);  // clamped image column
+        const int li = xx - lr;                     // its index in sL
+        const int xr = xx - d;                      // matching right-image column
+        const int ri = xr - rr;
+        float acc = 0.0f;
+#pragma unroll
+        for (int row = 0; row < NR; ++row) acc += (xr >= 0) ? fabsf(sL[row][li] - sR[row][ri]) : trunc;
+        col[i] = acc;
+    }
+#pragma unroll
+    for (int xi = 0; xi < TX; ++xi) {
+        const int x = x0 + xi;
+        if (x >= W) break;
+        float acc = 0.0f;
+#pragma unroll
+        for (int dx = 0; dx < NR; ++dx) acc += col[xi + dx];
+        out[((long long)y * W + x) * K + d] = (OT)fminf(trunc, acc * inv_area);
+    }
+}
+
+// Any odd window (the kernels above cover radii 1..3): one thread per (pixel, label).
 template <typename OT>
 __global__ __launch_bounds__(256) void sad_kernel(const float* __restrict__ IL, const float* __restrict__ IR, int W,
                                                   int H, int K, int r, float trunc, float inv_area,
@@ -52,6 +106,24 @@ __global__ __launch_bounds__(256) void contrast_kernel(const float* __restrict__
     }
 }
 
+// Whether the strips serve a volume of `size`-byte costs (same values either way).  A strip's
+// block does 64 x 4 pixels, so a frame needs 900 of them (3.5 per CU) to fill the chip: window
+// 3, FP16, row kernel -> strips 640x240x192 35 -> 34, 640x360x192 47 -> 36, 1242x375x192 88 -> 56
+// us, but 320x240x192 22 -> 29 and 96x72x192 11 -> 21 us.  Windows 5 and 7 keep 5 or 7 rows of
+// differences in registers, which leaves 2 labels a thread and reads LDS for each: better only
+// where the row kernel's waves are half empty, K <= 32 (1242x375x24 70 -> 43 us, x192 203 ->
+// 251 us at window 5).  One label a thread (odd K) writes parts of lines: beyond the 256 MB that
+// the last cache holds they no longer merge (1242x375, FP32, K = 135 81 -> 62, 201 112 -> 126 us).
+// Window 1 replaces a thread per cost with 64-bit divisions, whose time is the volume's size:
+// 320x240x32 11 -> 12, x64 14 -> 12 us.
+bool strip_serves(int r, const dm_shape& s, size_t size) {
+    const long long blocks = (long long)((s.W + kStripX - 1) / kStripX) * ((s.H + kStripY - 1) / kStripY);
+    const long long labels = (long long)s.W * s.H * s.K;
+    if (r == 0) return blocks >= 300 && labels >= 4000000;
+    if (r > 1) return r <= 3 && s.K <= 32 && blocks >= 900;
+    return blocks >= 900 && (s.K % 2 == 0 || labels * (long long)size <= (256LL << 20));
+}
+
 hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float inv_sigma, float* w_h,
                                    float* w_v, hipStream_t stream) {
     const long long npx = (long long)W * H;
@@ -79,7 +151,9 @@ hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw
 // quotient; n + 1 words in as many LDS banks), and a pixel's LPT costs are one vector store.
 // The block also writes the contrast weights of its pixels' edges.
 //
-// Measured, 1242 x 375 x 192 FP16, window 5, one view with the weights: see kCensusX.
+// Measured, 1242 x 375 x 192 FP16, window 5, both views with their weights: 128 -> 95 us (64
+// pixels a block and a pair of labels a thread before); 64, 128 and 256 pixels a block in one
+// comparison: 95.5, 92.0, 96.4 us.
 constexpr int kCensusX = 128, kCensusTX = 8;
 
 template <int R>
@@ -336,31 +410,51 @@ extern "C" int dm_build_cost_volume(const float* I_left, const float* I_right, d
     ProfScope ps(DM_PROF_COST_VOLUME, (double)total * (out_dtype == DM_F16 ? 2 : 4) + 8.0 * s.W * s.H, stream);
     hipError_t strip = hipSuccess;
     const StripWeights sw{w_h, w_v, p->lambda_pw, 1.0f / p->contrast_sigma};
+    const bool strips = strip_serves(r, s, out_dtype == DM_F16 ? 2 : 4);
+    const dim3 tgrid((unsigned)((s.W + kSadTX - 1) / kSadTX), (unsigned)s.H);
+    const dim3 tblock((unsigned)((s.K + 63) / 64 * 64));
 #define DM_SAD_STRIP(OT, RR)                                                                                        \
     strip = launch_sad_strip<OT, RR, -1>(I_left, I_right, s.W, s.H, s.K, 1, 0, 0, p->trunc, inv_area,               \
                                          static_cast<OT*>(cost_out), sw, stream)
+#define DM_SAD(OT, RR)                                                                                              \
+    if (strips)                                                                                                     \
+        DM_SAD_STRIP(OT, RR);                                                                                       \
+    else                                                                                                            \
+        hipLaunchKernelGGL((sad_tile_kernel<OT, RR>), tgrid, tblock, 0, stream, I_left, I_right, s.W, s.H, s.K,     \
+                           p->trunc, inv_area, static_cast<OT*>(cost_out))
     if (out_dtype == DM_F16) {
-        if (r == 0) DM_SAD_STRIP(_Float16, 0);
-        else if (r == 1) DM_SAD_STRIP(_Float16, 1);
-        else if (r == 2) DM_SAD_STRIP(_Float16, 2);
-        else if (r == 3) DM_SAD_STRIP(_Float16, 3);
-        else
+        if (r == 0 && strips) {
+            DM_SAD_STRIP(_Float16, 0);
+        } else if (r == 1) {
+            DM_SAD(_Float16, 1);
+        } else if (r == 2) {
+            DM_SAD(_Float16, 2);
+        } else if (r == 3) {
+            DM_SAD(_Float16, 3);
+        } else {
             hipLaunchKernelGGL(sad_kernel<_Float16>, dim3(blocks), dim3(256), 0, stream, I_left, I_right, s.W, s.H, s.K,
                                r, p->trunc, inv_area, static_cast<_Float16*>(cost_out));
+        }
     } else {
-        if (r == 0) DM_SAD_STRIP(float, 0);
-        else if (r == 1) DM_SAD_STRIP(float, 1);
-        else if (r == 2) DM_SAD_STRIP(float, 2);
-        else if (r == 3) DM_SAD_STRIP(float, 3);
-        else
+        if (r == 0 && strips) {
+            DM_SAD_STRIP(float, 0);
+        } else if (r == 1) {
+            DM_SAD(float, 1);
+        } else if (r == 2) {
+            DM_SAD(float, 2);
+        } else if (r == 3) {
+            DM_SAD(float, 3);
+        } else {
             hipLaunchKernelGGL(sad_kernel<float>, dim3(blocks), dim3(256), 0, stream, I_left, I_right, s.W, s.H, s.K, r,
                                p->trunc, inv_area, static_cast<float*>(cost_out));
+        }
     }
+#undef DM_SAD
 #undef DM_SAD_STRIP
     DM_HIP_TRY(strip, "sad strip launch");
     ps.stop();
     DM_HIP_TRY(hipGetLastError(), "sad launch");
-    if (r > 3 && (w_h != nullptr || w_v != nullptr))  // the strips wrote them otherwise
+    if (!strips && (w_h != nullptr || w_v != nullptr))  // the strips wrote them otherwise
         DM_HIP_TRY(launch_contrast_weights(I_left, s.W, s.H, p->lambda_pw, 1.0f / p->contrast_sigma, w_h, w_v, stream),
                    "contrast launch");
     return DM_OK;

@@ -18,7 +18,7 @@
 // The terms are added row by row within a column, then column by column.  The blocks of the
 // first labels j also write the contrast weights of A's edges, whose pixels they hold in LDS.
 //
-// Measured: 1242 x 375 x 192 FP16, window 3: 107 -> 53 us with the weights (3.4 TB/s; a block
+// Measured: 1242 x 375 x 192 FP16, window 3: 107 -> 62 us with the weights (2.9 TB/s; a block
 // of one row and 16 pixels with a label per thread before); 640 x 480 x 32 x 32 FP16 flow
 // volume 1214 -> 145 us (4.4 TB/s; a block per row and label j before).  8 rows a strip or 32
 // or 128 pixels: within 5 %; 16 rows: the differences no longer fit the registers (347 us).
