@@ -245,14 +245,25 @@ hipError_t launch_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st)
     if (a.T <= 3 && a.T - 1 <= t.LPL) {
         // the tile's message is the direct window: the same results bit for bit on any tile
         const Tile d = window_tile(a.K);
+        // ... but the naive minorant's two passes over columns at 3 full labels a lane: one wave
+        // has no more to do there than the chain wave (320x240x192, two iterations: 422 us with
+        // the columns in pipelines, 408 without; 96x480x192 378 and 369).
+        const bool light = d.LPL == 3 && a.K == d.G * d.LPL && a.theta == nullptr && a.mode == kModeNaive;
 #define DM_PIPE_CASE(g, l) \
-    if (d.G == g && d.LPL == l && pipe_fits(d, a)) return launch_pipe<g, l, false>(a, dt, st);
+    if (d.G == g && d.LPL == l && !light && pipe_fits(d, a)) return launch_pipe<g, l, false>(a, dt, st);
         DM_FOR_EACH_PIPE(DM_PIPE_CASE)
 #undef DM_PIPE_CASE
     } else {
-        // the scans round by tile: the same tile
+        // The scans round by tile: the same tile.  Their steps are most of a node and on the
+        // chain wave either way, so the pipeline gains what the one-wave kernel spends on single
+        // accesses to a partial tile (T = 5, 320x240: K = 100 1.45, K = 33 1.29 times as fast; on
+        // the full tiles K = 64 and 256 0.90), and where the chain wave is the widest tile's or
+        // scans across more than 4 lanes only with a CU for each workgroup (T = 8, K = 210:
+        // 320x240 1.19, 640x480 0.95; T = 30, K = 80: 1280x400 0.91).
+        const int per_cu = t.G * t.LPL == 256 || a.T - 1 > 4 * t.LPL ? 1 : 16;
+        const bool gains = a.K != t.G * t.LPL && a.n_chains <= 64 / t.G * 256 * per_cu;
 #define DM_PIPE_CASE(g, l) \
-    if (t.G == g && t.LPL == l && pipe_fits(t, a)) return launch_pipe<g, l, true>(a, dt, st);
+    if (t.G == g && t.LPL == l && gains && pipe_fits(t, a)) return launch_pipe<g, l, true>(a, dt, st);
         DM_FOR_EACH_PIPE_SCAN(DM_PIPE_CASE)
 #undef DM_PIPE_CASE
     }
