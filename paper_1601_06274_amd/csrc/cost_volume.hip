@@ -6,15 +6,16 @@
 // (Sec. 3.1); this kernel provides a truncated windowed SAD in the same role.
 // Edge strengths are image dependent, lower across image edges (Sec. 2.1).
 //
-// Layout: the volume is label-major ([y][x][d], d fastest).  Small windows of large
-// frames are computed on strips of rows (sad_strip.h), others a row at a time.  Border handling: window positions are clamped to the
-// image (clamp-to-edge), and a right-image column left of 0 costs `trunc`.
+// Layout: the volume is label-major ([y][x][d], d fastest).  Windows up to 7 of large frames
+// are computed on strips of rows (sad_strip.h), others a row at a time.  Border handling:
+// window positions are clamped to the image (clamp-to-edge), and a right-image column left
+// of 0 costs `trunc`.
 #include "common.h"
 #include "sad_strip.h"
 
 namespace dm {
 
-// Small frames and wide windows: a block owns one row and kSadTX pixels, its threads are the
+// Small frames: a block owns one row and kSadTX pixels, its threads are the
 // labels (K <= 256 -> 1..4 waves), so each pixel's K costs are one coalesced write.  Each
 // thread sums the window vertically for the TX + 2R window columns of its label, then slides
 // the horizontal sum: the same sums in the same order as the strips'.
@@ -109,10 +110,10 @@ __global__ __launch_bounds__(256) void contrast_kernel(const float* __restrict__
 // Whether the strips serve a volume of `size`-byte costs (same values either way).  A strip's
 // block does 64 x 4 pixels, so a frame needs 900 of them (3.5 per CU) to fill the chip: window
 // 3, FP16, row kernel -> strips 640x240x192 35 -> 34, 640x360x192 47 -> 36, 1242x375x192 88 -> 56
-// us, but 320x240x192 22 -> 29 and 96x72x192 11 -> 21 us.  Windows 5 and 7 keep 5 or 7 rows of
-// differences in registers, which leaves 2 labels a thread and reads LDS for each: better only
-// where the row kernel's waves are half empty, K <= 32 (1242x375x24 70 -> 43 us, x192 203 ->
-// 251 us at window 5).  One label a thread (odd K) writes parts of lines: beyond the 256 MB that
+// us, but 320x240x192 22 -> 29 and 96x72x192 11 -> 21 us.  Windows 5 and 7 share more of a row's
+// differences and need fewer blocks for it: 320x240x201 44 -> 50 us at window 5, but 640x240x201
+// 83 -> 56, x192 72 -> 41, x24 27 -> 14 us, and at window 7 144 -> 75, 119 -> 69, 44 -> 18 us.
+// One label a thread (odd K) writes parts of lines: beyond the 256 MB that
 // the last cache holds they no longer merge (1242x375, FP32, K = 135 81 -> 62, 201 112 -> 126 us).
 // Window 1 replaces a thread per cost with 64-bit divisions, whose time is the volume's size:
 // 320x240x32 11 -> 12, x64 14 -> 12 us.
@@ -120,7 +121,7 @@ bool strip_serves(int r, const dm_shape& s, size_t size) {
     const long long blocks = (long long)((s.W + kStripX - 1) / kStripX) * ((s.H + kStripY - 1) / kStripY);
     const long long labels = (long long)s.W * s.H * s.K;
     if (r == 0) return blocks >= 300 && labels >= 4000000;
-    if (r > 1) return r <= 3 && s.K <= 32 && blocks >= 900;
+    if (r > 1) return r <= 3 && blocks >= 600;
     return blocks >= 900 && (s.K % 2 == 0 || labels * (long long)size <= (256LL << 20));
 }
 

@@ -19,10 +19,16 @@
 // first labels j also write the contrast weights of A's edges, whose pixels they hold in LDS.
 //
 // Measured: 1242 x 375 x 192 FP16, window 3: 107 -> 62 us with the weights (2.9 TB/s; a block
-// of one row and 16 pixels with a label per thread before); 640 x 480 x 32 x 32 FP16 flow
-// volume 1214 -> 145 us (4.4 TB/s; a block per row and label j before).  8 rows a strip or 32
-// or 128 pixels: within 5 %; 16 rows: the differences no longer fit the registers (347 us).
+// of one row and 16 pixels with a label per thread before), window 5 203 -> 83 us; flow volume
+// of 640 x 480 x 32 x 32 FP16, window 3 1214 -> 145 us (4.4 TB/s; a block per row and label j
+// before), window 5 4887 -> 217 us (661 with the ring of differences in scratch memory).
+// 8 rows a strip: that stereo volume 52 -> 48 us and the flow volumes 146 -> 140, 217 -> 186,
+// but half as many blocks, so 1242 x 375 x 24 1.4 times and 320 x 240 x 17 x 15 1.3 times the
+// time; 16 rows: the stereo volume 90 us.
 #pragma once
+
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -45,6 +51,12 @@ struct StripWeights {
     float *w_h, *w_v;
     float lambda_pw, inv_sigma;
 };
+
+// f(0), f(1), ... with constants, until one is false
+template <class F, int... S>
+__device__ __forceinline__ void strip_steps(F& f, std::integer_sequence<int, S...>) {
+    (f(std::integral_constant<int, S>()) && ...);
+}
 
 template <typename OT, int R, int DIR, int LPT>
 __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict__ A, const float* __restrict__ B, int W,
@@ -95,9 +107,11 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
         const float* a0 = sA + g * TX;
         // label i0 + l at window column c: b0[c + l] (flow) or b0[c + LPT - 1 - l] (stereo)
         const float* b0 = sB + g * TX + (DIR > 0 ? i0 : K - 1 - i0);
+        // The ring of row differences: a step's index into it is a compile-time constant (indexed by a
+        // loop variable it stays in scratch memory for R >= 2).
         float e[NR][LPT][NC];
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
+        auto step = [&](auto row) __attribute__((always_inline)) {
+            constexpr int s = decltype(row)::value;
             const int cy = min(max(y0 - R + s, 0), H - 1);  // the window row's (clamped) image row
             const int my = cy + d2;
             float(&es)[LPT][NC] = e[s % NR];
@@ -135,36 +149,39 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
                     for (int c = R - 1; c >= 0; --c) es[l][c] = xa - R + c < 0 ? es[l][c + 1] : es[l][c];
                 }
             }
-            if (s < 2 * R) continue;
-            const int y = y0 + s - 2 * R;
-            if (y >= H) break;
-            float col[LPT][NC];
+            if constexpr (s >= 2 * R) {
+                const int y = y0 + s - 2 * R;  // the output row that this window row completes
+                if (y >= H) return false;
+                float col[LPT][NC];
 #pragma unroll
-            for (int l = 0; l < LPT; ++l)
+                for (int l = 0; l < LPT; ++l)
 #pragma unroll
-                for (int c = 0; c < NC; ++c) {
-                    float acc = e[(s - 2 * R) % NR][l][c];
+                    for (int c = 0; c < NC; ++c) {
+                        float acc = e[(s - 2 * R) % NR][l][c];
 #pragma unroll
-                    for (int r = 1; r < NR; ++r) acc += e[(s - 2 * R + r) % NR][l][c];
-                    col[l][c] = acc;
-                }
-            OT* o = out + (((long long)y * W + xa) * K2 + j) * K + i0;
-#pragma unroll
-            for (int q = 0; q < TX; ++q) {
-                if (xa + q < W) {
-                    typedef OT vec_t __attribute__((ext_vector_type(LPT)));
-                    vec_t r;
-#pragma unroll
-                    for (int l = 0; l < LPT; ++l) {
-                        float acc = col[l][q];
-#pragma unroll
-                        for (int dx = 1; dx < NR; ++dx) acc += col[l][q + dx];
-                        r[l] = (OT)fminf(trunc, acc * inv_area);
+                        for (int r = 1; r < NR; ++r) acc += e[(s - 2 * R + r) % NR][l][c];
+                        col[l][c] = acc;
                     }
-                    *reinterpret_cast<vec_t*>(o + (long long)q * K2 * K) = r;
+                OT* o = out + (((long long)y * W + xa) * K2 + j) * K + i0;
+#pragma unroll
+                for (int q = 0; q < TX; ++q) {
+                    if (xa + q < W) {
+                        typedef OT vec_t __attribute__((ext_vector_type(LPT)));
+                        vec_t r;
+#pragma unroll
+                        for (int l = 0; l < LPT; ++l) {
+                            float acc = col[l][q];
+#pragma unroll
+                            for (int dx = 1; dx < NR; ++dx) acc += col[l][q + dx];
+                            r[l] = (OT)fminf(trunc, acc * inv_area);
+                        }
+                        *reinterpret_cast<vec_t*>(o + (long long)q * K2 * K) = r;
+                    }
                 }
             }
-        }
+            return true;
+        };
+        strip_steps(step, std::make_integer_sequence<int, NS>());
     }
 }
 
