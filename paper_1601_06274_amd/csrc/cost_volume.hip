@@ -195,7 +195,7 @@ __global__ __launch_bounds__(256) void census_tile_kernel(const float* __restric
     __shared__ float sA[NR][kCensusX + 2 * R];
     __shared__ float sB[NR][kCensusX + 255 + 2 * R];
     __shared__ code_t cA[kCensusX];
-    __shared__ code_t cB[kCensusX + 255 + 2 * (LPT - 1)];  // codes from LPT - 1 on; padded for labels beyond K
+    __shared__ code_t cB[kCensusX + 255];
     __shared__ float lut[64];
     const float* __restrict__ A = LEFT ? IL : IR;  // reference image of the view
     const float* __restrict__ B = LEFT ? IR : IL;  // matched image
@@ -222,9 +222,9 @@ __global__ __launch_bounds__(256) void census_tile_kernel(const float* __restric
         if (sw.w_v != nullptr && x < W && y + 1 < H)
             sw.w_v[(long long)y * W + x] = contrast_weight(sA[R + 1][c + R], sA[R][c + R], sw.lambda_pw, sw.inv_sigma);
     }
-    for (int c = threadIdx.x; c < nb; c += blockDim.x) cB[LPT - 1 + c] = census_code<R>(sB, c);
+    for (int c = threadIdx.x; c < nb; c += blockDim.x) cB[c] = census_code<R>(sB, c);
     __syncthreads();
-    const int groups = (K + LPT - 1) / LPT;
+    const int groups = K / LPT;  // LPT divides K
     const bool interior = bB >= 0 && bB + nb <= W && x0 + kCensusX <= W;
     for (int item = threadIdx.x; item < (kCensusX / TX) * groups; item += blockDim.x) {
         const int g = item / groups;
@@ -232,7 +232,7 @@ __global__ __launch_bounds__(256) void census_tile_kernel(const float* __restric
         const int xa = x0 + g * TX;
         if (xa >= W) continue;
         // pixel q and label i0 + l meet code vb[q + LPT - 1 - l] (left) or vb[q + l] (right)
-        const code_t* b = cB + g * TX + (LEFT ? K - 1 - i0 : i0 + LPT - 1);
+        const code_t* b = cB + g * TX + (LEFT ? K - LPT - i0 : i0);
         code_t va[TX], vb[TX + LPT - 1];
 #pragma unroll
         for (int q = 0; q < TX; ++q) va[q] = cA[g * TX + q];
@@ -321,7 +321,7 @@ extern "C" int dm_build_cost_volume_census(const float* I_left, const float* I_r
     // the widest vector that K and the volume's alignment allow; the items spread evenly
     const int lpt = (s.K % 4 == 0 && (uintptr_t)cost_out % (4 * es) == 0) ? 4
                     : (s.K % 2 == 0 && (uintptr_t)cost_out % (2 * es) == 0) ? 2 : 1;
-    const int items = (kCensusX / kCensusTX) * ((s.K + lpt - 1) / lpt), turns = (items + 255) / 256;
+    const int items = (kCensusX / kCensusTX) * (s.K / lpt), turns = (items + 255) / 256;
     const dim3 block((unsigned)(((items + turns - 1) / turns + 63) / 64 * 64));
 #define DM_CENSUS_V(OT, RR, LF, LP)                                                                                 \
     hipLaunchKernelGGL((census_tile_kernel<OT, RR, LF, LP>), grid, block, 0, stream, I_left, I_right, s.W, s.H, s.K, \

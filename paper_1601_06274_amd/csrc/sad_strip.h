@@ -39,11 +39,9 @@ constexpr int kStripTX = 8;  // pixels per thread
 constexpr int kStripY = 4;   // rows per block
 constexpr int kStripJ = 4;   // labels j per block
 
-// LDS floats of a block (staged rows of A and B; B's rows padded by LPT - 1 columns for the
-// labels that a partial last group does not have).
-constexpr size_t strip_lds_floats(int R, int K, int nj, int LPT) {
-    return (size_t)(kStripY + 2 * R) * (kStripX + 2 * R) +
-           (size_t)(kStripY + 2 * R + nj - 1) * (kStripX + 2 * R + K - 1 + LPT - 1);
+// LDS floats of a block (staged rows of A and B).
+constexpr size_t strip_lds_floats(int R, int K, int nj) {
+    return (size_t)(kStripY + 2 * R) * (kStripX + 2 * R) + (size_t)(kStripY + 2 * R + nj - 1) * (kStripX + 2 * R + K - 1);
 }
 
 // Contrast weights to write beside the volume (null: not wanted).
@@ -67,9 +65,9 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
     extern __shared__ float strip_lds[];
     float* sA = strip_lds;               // [NS][colsA]
     float* sB = strip_lds + NS * colsA;  // [NS + nj - 1][colsB]
-    const int colsB = kStripX + 2 * R + K - 1 + LPT - 1;
+    const int colsB = kStripX + 2 * R + K - 1;
     const int x0 = blockIdx.x * kStripX, y0 = blockIdx.y * kStripY, j0 = blockIdx.z * nj;
-    const int cb0 = x0 - R + (DIR > 0 ? -off1 : -(K - 1) - (LPT - 1));  // image column of sB[.][0]
+    const int cb0 = x0 - R + (DIR > 0 ? -off1 : -(K - 1));  // image column of sB[.][0]
     const int rb0 = y0 - R + j0 - off2;                                 // image row of sB[0]
     const int wave = threadIdx.x / 64, lane = threadIdx.x % 64, waves = blockDim.x / 64;
     for (int s = wave; s < NS; s += waves) {
@@ -92,7 +90,7 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
             }
         }
     }
-    const int groups = (K + LPT - 1) / LPT;  // label groups of a pixel
+    const int groups = K / LPT;  // label groups of a pixel (LPT divides K)
     const int items = (kStripX / TX) * nj * groups;
     // every column of A and B that the block reaches lies in the image
     const bool interior = x0 - R >= 0 && x0 + kStripX + R <= W && cb0 >= 0 && cb0 + colsB <= W;
@@ -106,7 +104,7 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
         if (xa >= W || j >= K2) continue;
         const float* a0 = sA + g * TX;
         // label i0 + l at window column c: b0[c + l] (flow) or b0[c + LPT - 1 - l] (stereo)
-        const float* b0 = sB + g * TX + (DIR > 0 ? i0 : K - 1 - i0);
+        const float* b0 = sB + g * TX + (DIR > 0 ? i0 : K - LPT - i0);
         // The ring of row differences: a step's index into it is a compile-time constant (indexed by a
         // loop variable it stays in scratch memory for R >= 2).
         float e[NR][LPT][NC];
@@ -200,12 +198,12 @@ hipError_t launch_sad_strip(const float* A, const float* B, int W, int H, int K,
     auto fits = [&](int lpt) { return K % lpt == 0 && (uintptr_t)out % (lpt * sizeof(OT)) == 0; };
     // at most 256 threads, the items spread evenly over their turns
     auto block = [&](int lpt) {
-        const int items = (kStripX / kStripTX) * nj * ((K + lpt - 1) / lpt), turns = (items + 255) / 256;
+        const int items = (kStripX / kStripTX) * nj * (K / lpt), turns = (items + 255) / 256;
         return dim3((unsigned)(((items + turns - 1) / turns + 63) / 64 * 64));
     };
 #define DM_STRIP(LPT)                                                                                              \
     hipLaunchKernelGGL((sad_strip_kernel<OT, R, DIR, LPT>), grid, block(LPT),                                      \
-                       strip_lds_floats(R, K, nj, LPT) * sizeof(float), st, A, B, W, H, K, K2, off1, off2, nj, trunc, \
+                       strip_lds_floats(R, K, nj) * sizeof(float), st, A, B, W, H, K, K2, off1, off2, nj, trunc, \
                        inv_area, out, sw)
     if constexpr (R <= 1) {
         if (fits(4)) {
