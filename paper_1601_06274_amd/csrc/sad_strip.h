@@ -105,11 +105,12 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
         const float* a0 = sA + g * TX;
         // label i0 + l at window column c: b0[c + l] (flow) or b0[c + LPT - 1 - l] (stereo)
         const float* b0 = sB + g * TX + (DIR > 0 ? i0 : K - LPT - i0);
-        // The ring of row differences: a step's index into it is a compile-time constant (indexed by a
-        // loop variable it stays in scratch memory for R >= 2).
+        // The ring of row differences: for R >= 2 a step's index into it is a compile-time constant
+        // (indexed by a loop variable it stays in scratch memory); for R <= 1 the compiler resolves
+        // the loop's and schedules it better (flow 160 x 120 x 17 x 15, window 3, 16.5 and 17.1 us).
         float e[NR][LPT][NC];
         auto step = [&](auto row) __attribute__((always_inline)) {
-            constexpr int s = decltype(row)::value;
+            const int s = row;
             const int cy = min(max(y0 - R + s, 0), H - 1);  // the window row's (clamped) image row
             const int my = cy + d2;
             float(&es)[LPT][NC] = e[s % NR];
@@ -147,7 +148,7 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
                     for (int c = R - 1; c >= 0; --c) es[l][c] = xa - R + c < 0 ? es[l][c + 1] : es[l][c];
                 }
             }
-            if constexpr (s >= 2 * R) {
+            if (s >= 2 * R) {
                 const int y = y0 + s - 2 * R;  // the output row that this window row completes
                 if (y >= H) return false;
                 float col[LPT][NC];
@@ -179,7 +180,13 @@ __global__ __launch_bounds__(256) void sad_strip_kernel(const float* __restrict_
             }
             return true;
         };
-        strip_steps(step, std::make_integer_sequence<int, NS>());
+        if constexpr (R >= 2) {
+            strip_steps(step, std::make_integer_sequence<int, NS>());
+        } else {
+#pragma unroll
+            for (int s = 0; s < NS; ++s)
+                if (!step(s)) break;
+        }
     }
 }
 
