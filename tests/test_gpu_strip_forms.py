@@ -22,3 +22,24 @@ def test_wide_windows_many_labels(window, K, dtype):
     torch.cuda.synchronize()
     for name, x, y in zip(("cost", "w_h", "w_v"), got, want):
         assert torch.equal(x, y), f"{name} differs"
+
+
+@pytest.mark.parametrize("window", [1, 3, 5])
+@pytest.mark.parametrize("K1,K2", [(64, 5), (31, 13), (17, 15), (48, 3), (3, 64)])
+def test_flow_small_frames(K1, K2, window):
+    """Frames of few strips, whose blocks take fewer labels j, against the rows of a tall frame."""
+    from paper_1601_06274_amd import ops
+    H, W, R = 1100, 70, window // 2
+    print(f"[case] flow {K1}x{K2} window {window}", flush=True)
+    g = torch.Generator().manual_seed(K1)
+    I1, I2 = (torch.rand((H, W), generator=g).cuda() for _ in range(2))
+    kw = dict(window=window, trunc=0.4, dtype=torch.float16)
+    got = ops.build_flow_cost_volume(I1, I2, K1, K2, K1 // 2, K2 // 2, **kw)
+    halo = R + K2  # the rows of both images that a row's costs reach
+    for y in (0, 301, H - 9):
+        a, b = max(y - halo, 0), min(y + 9 + halo, H)
+        want = ops.build_flow_cost_volume(I1[a:b].contiguous(), I2[a:b].contiguous(), K1, K2, K1 // 2, K2 // 2, **kw)
+        torch.cuda.synchronize()
+        assert torch.equal(got[0][y:y + 9], want[0][y - a:y - a + 9]), f"cost differs at row {y}"
+        assert torch.equal(got[1][y:y + 9], want[1][y - a:y - a + 9])
+        assert torch.equal(got[2][y:y + 8], want[2][y - a:y - a + 8])
