@@ -218,6 +218,16 @@ Tile default_tile(int K) {
     return best;
 }
 
+int cu_count() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return 256;
+    }
+    return n;
+}
+
 Tile row_tile(const dm_shape& s, const dm_discrete_params& p) {
     return p.tile_lanes != 0 ? Tile{p.tile_lanes, p.labels_per_lane} : default_tile(s.K);
 }
@@ -233,37 +243,20 @@ hipError_t launch_tile_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_
     return hipErrorInvalidValue;
 }
 
-// Whether the pipelined sweeps serve a launch on tile d: its workgroups are all resident.
-// Beyond that a second round of workgroups costs as much again, while the one-wave kernel is
-// at HBM bandwidth (1242 columns of K = 192: 826 us against about 2 x 600).
-bool pipe_fits(Tile d, const SweepArgs& a) {
-    const int blocks = (a.n_chains + 64 / d.G - 1) / (64 / d.G);
-    return (a.mode & kRecordFlag) == 0 && blocks <= pipe_resident(d.LPL, a.theta != nullptr);
-}
-
+// The pipelined sweeps where they gain (pipe_per_cu), else one wave per chain.
 hipError_t launch_sweep(Tile t, const SweepArgs& a, dm_dtype dt, hipStream_t st) {
-    if (a.T <= 3 && a.T - 1 <= t.LPL) {
-        // the tile's message is the direct window: the same results bit for bit on any tile
-        const Tile d = window_tile(a.K);
-        // ... but the naive minorant's two passes over columns at 3 full labels a lane: one wave
-        // has no more to do there than the chain wave (320x240x192, two iterations: 422 us with
-        // the columns in pipelines, 408 without; 96x480x192 378 and 369).
-        const bool light = d.LPL == 3 && a.K == d.G * d.LPL && a.theta == nullptr && a.mode == kModeNaive;
+    // window messages: the same results bit for bit on any tile; scans round by tile
+    const bool scan = !(a.T <= 3 && a.T - 1 <= t.LPL);
+    const Tile d = scan ? t : window_tile(a.K);
+    const int blocks = (a.n_chains + 64 / d.G - 1) / (64 / d.G);
+    const int per_cu = pipe_per_cu(d, t, scan, a.T, a.K, a.theta != nullptr, dt == DM_F16);
+    if ((a.mode & kRecordFlag) == 0 && blocks <= per_cu * cu_count()) {
 #define DM_PIPE_CASE(g, l) \
-    if (d.G == g && d.LPL == l && !light && pipe_fits(d, a)) return launch_pipe<g, l, false>(a, dt, st);
+    if (!scan && d.G == g && d.LPL == l) return launch_pipe<g, l, false>(a, dt, st);
         DM_FOR_EACH_PIPE(DM_PIPE_CASE)
 #undef DM_PIPE_CASE
-    } else {
-        // The scans round by tile: the same tile.  Their steps are most of a node and on the
-        // chain wave either way, so the pipeline gains what the one-wave kernel spends on single
-        // accesses to a partial tile (T = 5, 320x240: K = 100 1.45, K = 33 1.29 times as fast; on
-        // the full tiles K = 64 and 256 0.90), and where the chain wave is the widest tile's or
-        // scans across more than 4 lanes only with a CU for each workgroup (T = 8, K = 210:
-        // 320x240 1.19, 640x480 0.95; T = 30, K = 80: 1280x400 0.91).
-        const int per_cu = t.G * t.LPL == 256 || a.T - 1 > 4 * t.LPL ? 1 : 16;
-        const bool gains = a.K != t.G * t.LPL && a.n_chains <= 64 / t.G * 256 * per_cu;
 #define DM_PIPE_CASE(g, l) \
-    if (t.G == g && t.LPL == l && gains && pipe_fits(t, a)) return launch_pipe<g, l, true>(a, dt, st);
+    if (scan && d.G == g && d.LPL == l) return launch_pipe<g, l, true>(a, dt, st);
         DM_FOR_EACH_PIPE_SCAN(DM_PIPE_CASE)
 #undef DM_PIPE_CASE
     }

@@ -38,30 +38,13 @@
 
 #include "batched_kernels.h"
 #include "dmm_kernels.h"
+#include "pipe_rule.h"
 
 namespace dm {
 
-// Nodes between two barriers, and nodes in flight in the loader's register ring
-constexpr int pipe_chunk(int lpl) { return lpl == 1 ? 8 : 4; }
-// (fewer where their registers would pass 256: values moved to the accumulation registers
-// would be waited for as they arrive).
+// Nodes in flight in the loader's register ring (fewer where their registers would pass 256:
+// values moved to the accumulation registers would be waited for as they arrive).
 constexpr int pipe_ahead(int lpl, bool theta) { return lpl <= 2 ? 16 : (lpl == 3 ? (theta ? 12 : 16) : (theta ? 8 : 12)); }
-constexpr int kPipeBufs = 4;  // staging buffers (chunks)
-// staged words of a node and lane: unary[LPL], reverse message[LPL] and, for rows (the
-// columns' unary is the dual itself), dual[LPL]
-constexpr int pipe_in_words(int lpl, bool theta) { return (theta ? 3 : 2) * lpl; }
-// result words: min-marginal[LPL], message[LPL]; of a message pass (which has no
-// min-marginals) word LPL - 1 is the minimum
-constexpr int pipe_out_words(int lpl) { return 2 * lpl; }
-// Words are kept in groups of 4 (one 16-byte LDS access); a last group of 3 takes 4.
-constexpr int pipe_padded(int w) { return w % 4 == 3 ? w + 1 : w; }
-// LDS words of the staging records, the result records and the edge weights (of a chunk:
-// word q of a group's lanes is the weight of its node q)
-constexpr int pipe_in_lds(int lpl, bool theta) { return 64 * pipe_chunk(lpl) * kPipeBufs * pipe_padded(pipe_in_words(lpl, theta)); }
-constexpr int pipe_out_lds(int lpl) { return 64 * pipe_chunk(lpl) * 2 * pipe_padded(pipe_out_words(lpl)); }
-constexpr int pipe_lds_words(int lpl, bool theta) { return pipe_in_lds(lpl, theta) + pipe_out_lds(lpl) + 64 * kPipeBufs; }
-// workgroups that 256 CUs hold at once by their LDS (160 KB per CU, given in units of 1280 bytes)
-constexpr int pipe_resident(int lpl, bool theta) { return 256 * (163840 / ((4 * pipe_lds_words(lpl, theta) + 1279) / 1280 * 1280)); }
 
 using lds_u32 = __attribute__((address_space(3))) uint32_t;
 typedef uint32_t pipe_u4 __attribute__((ext_vector_type(4)));
@@ -312,12 +295,8 @@ struct PipeChain {
 };
 
 // ------------------------------------------------------------------ loader
-// VEC: every lane's labels exist or none do (K is a multiple of the labels per lane), so a
-// lane's values move as one vector; else one access per label.
-template <int LPL, typename TT, bool HAS_THETA>
-bool pipe_vec(int K) {
-    return K % LPL == 0 && !(HAS_THETA && sizeof(TT) == 2 && K % 2 != 0);  // FP16 costs are read as dwords
-}
+// VEC: every lane's labels exist or none do (pipe_vec), so a lane's values move as one
+// vector; else one access per label.
 // Node offsets: a lane's offset in a volume is fixed (its label at node 0; out of range for
 // labels and chains that do not exist), the node's offset is scalar and stays inside the
 // chain.  Nodes beyond the end are loaded at an out-of-range lane offset: no access, as the
@@ -797,7 +776,7 @@ hipError_t launch_pipe_full(const SweepArgs& a, hipStream_t st) {
 template <int G, int LPL, bool SCAN, typename TT, bool HAS_THETA>
 hipError_t launch_pipe_tt(const SweepArgs& a, hipStream_t st) {
     if constexpr (LPL > 1)
-        if (!pipe_vec<LPL, TT, HAS_THETA>(a.K)) return launch_pipe_full<G, LPL, SCAN, TT, false, HAS_THETA>(a, st);
+        if (!pipe_vec(a.K, LPL, HAS_THETA, sizeof(TT) == 2)) return launch_pipe_full<G, LPL, SCAN, TT, false, HAS_THETA>(a, st);
     return launch_pipe_full<G, LPL, SCAN, TT, true, HAS_THETA>(a, st);
 }
 
