@@ -15,7 +15,7 @@
 #include "common.h"
 #include "plan.h"
 #include "refine.h"
-#include "tiles.h"
+#include "pipe_rule.h"
 
 namespace dm {
 
@@ -48,8 +48,8 @@ hipError_t launch_pipe_class(int G, int LPL, const BatchLaunch& bl, bool full, d
     return hipErrorInvalidValue;
 }
 
-// Direct window messages (T <= 3) on every chain tile that holds K labels: the pipelined
-// sweeps give those tiles' results bit for bit.
+// Whether the pipelined sweeps give a chain tile's results bit for bit: direct window messages
+// (T <= 3; tile_lpl 0: on every tile that the autotuner may choose).
 bool pipe_serves(int K, int T, int tile_lpl) { return T <= 3 && (tile_lpl != 0 ? T - 1 <= tile_lpl : K > 4); }
 
 __global__ void zero_i32_kernel(int* __restrict__ p, long long n) {
@@ -206,7 +206,31 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
         return DM_ERR_HIP;
     };
 
+    int dev = 0, n_cu = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
+
     // 1. tiles per (K, family): given in p, else autotuned on the largest instance of that K
+    // (not needed where both families are pipelined); gains: the pipelines gain there
+    std::map<int, std::pair<bool, bool>> gains_of_k;
+    for (int i = 0; i < n; ++i) {
+        const int K = inst[i].s.K;
+        if (gains_of_k.count(K)) continue;
+        const Tile d = window_tile(K);
+        Tile t[2] = {{p->tile_lanes, p->labels_per_lane}, {p->tile_lanes_v, p->labels_per_lane_v}};
+        if (t[0].G == 0) (void)dm_default_tile(K, &t[0].G, &t[0].LPL);
+        if (t[1].G == 0 || p->tile_lanes == 0) t[1] = t[0];
+        long long blocks[2] = {0, 0}, bytes = 0;
+        const int cpw = 64 / d.G;
+        for (int j = 0; j < n; ++j) {
+            if (inst[j].s.K != K) continue;
+            blocks[0] += (inst[j].s.H + cpw - 1) / cpw;
+            blocks[1] += (inst[j].s.W + cpw - 1) / cpw;
+            bytes += (long long)inst[j].s.W * inst[j].s.H * K * 4;
+        }
+        gains_of_k[K] = {pipe_plan_serves(d, t[0], K, blocks[0], bytes, n_cu),
+                         pipe_plan_serves(d, t[1], K, blocks[1], bytes, n_cu)};
+    }
     std::map<int, std::pair<std::pair<int, int>, std::pair<int, int>>> tile_of_k;
     for (int i = 0; i < n; ++i) {
         const int K = inst[i].s.K;
@@ -217,7 +241,7 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
                 big = j;
         dm_discrete_params q = *p;
         q.keep_checkpoints = 0;
-        if (p->tile_lanes == 0 && pipe_serves(K, p->trunc_T, 0)) continue;  // no chain tile needed
+        if (p->tile_lanes == 0 && pipe_serves(K, p->trunc_T, 0) && gains_of_k[K].first && gains_of_k[K].second) continue;
         if (p->tile_lanes == 0) {
             q.tile_lanes = q.labels_per_lane = q.tile_lanes_v = q.labels_per_lane_v = 0;
             const int st = dm_autotune_tiles(inst[big].s, cost_dtype, &q, nullptr);
@@ -292,7 +316,7 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
             const int K = inst[i].s.K;
             std::pair<int, int> t{0, 0};
             if (tile_of_k.count(K)) t = fam == 0 ? tile_of_k[K].first : tile_of_k[K].second;
-            const bool pipe = pipe_serves(K, p->trunc_T, t.second);
+            const bool pipe = pipe_serves(K, p->trunc_T, t.second) && (fam == 0 ? gains_of_k[K].first : gains_of_k[K].second);
             if (pipe) {
                 const Tile w = window_tile(K);
                 t = {w.G, w.LPL};
@@ -385,9 +409,6 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
     }
 
     // 5. capture the whole solve into one graph
-    int dev = 0, n_cu = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev);
     constexpr int kSide = 4;
     hipStream_t main_s = nullptr, side[kSide] = {};
     hipEvent_t ev_fork = nullptr, ev_join[kSide] = {};

@@ -77,4 +77,18 @@ inline int pipe_per_cu(Tile d, Tile t, bool scan, int T, int K, bool theta, bool
     return !theta && t.LPL == 3 ? 3 : lds;
 }
 
+// Whether a batched plan pipelines the chains of one label count and family (`blocks` workgroups,
+// `bytes` in their FP32 dual volumes).  More workgroups than the chip holds follow each other and
+// every chain still gains by its length, but on a filled tile of many chains a wave (t) whose
+// volumes stay near the last cache (256 MB) the plan is bound by issue, and a wave for one or two
+// chains issues more.  Measured, one-wave queue / pipelines, iterative and naive minorant:
+// 96 frames of 96 x 72 K = 32 0.88 and 0.80, K = 64 0.86, 0.71, K = 96 0.88, 0.79 (71 .. 212 MB);
+// 24 of 320 x 240 K = 32 0.98, 0.89 (236 MB), 48 of them 1.09, 1.03, K = 64 1.09, 1.03 (472 MB);
+// with up to 8 workgroups a CU (two labels a lane: 12) 12 of 320 x 240 K = 32 1.13, 1.13, 24 of
+// 160 x 120 K = 128 1.07, 1.03.
+inline bool pipe_plan_serves(Tile d, Tile t, int K, long long blocks, long long bytes, int cus) {
+    if (t.G * t.LPL != K || d.G < 32 || d.LPL > 2) return true;
+    return blocks <= (long long)(d.LPL == 1 ? 8 : 12) * cus || bytes > (256LL << 20);
+}
+
 }  // namespace dm
