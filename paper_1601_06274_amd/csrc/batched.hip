@@ -244,7 +244,7 @@ extern "C" int dm_plan_batched(const dm_instance* inst, int n, dm_dtype cost_dty
         if (p->tile_lanes == 0 && pipe_serves(K, p->trunc_T, 0) && gains_of_k[K].first && gains_of_k[K].second) continue;
         if (p->tile_lanes == 0) {
             q.tile_lanes = q.labels_per_lane = q.tile_lanes_v = q.labels_per_lane_v = 0;
-            const int st = dm_autotune_tiles(inst[big].s, cost_dtype, &q, nullptr);
+            const int st = autotune_tiles(inst[big].s, cost_dtype, &q, true, nullptr);  // the queue's kernels
             if (st != DM_OK) {
                 delete plan;
                 return st;

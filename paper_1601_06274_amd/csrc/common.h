@@ -43,6 +43,7 @@ __device__ __forceinline__ float contrast_weight(float neighbour, float c, float
 hipError_t launch_contrast_weights(const float* I, int W, int H, float lambda_pw, float inv_sigma, float* w_h,
                                    float* w_v, hipStream_t stream);
 int validate_discrete(const dm_shape& s, const dm_discrete_params* p);
+int autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_params* p, bool one_wave, void* hip_stream);  // dmm.hip
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 

@@ -957,9 +957,11 @@ __global__ void hash_fill_kernel(float* __restrict__ f32, _Float16* __restrict__
 }
 
 struct TuneKey {
-    int W, H, K, dt, minorant, max_pass;
+    int W, H, K, dt, minorant, max_pass, scan_T;  // scan_T: 0 for window messages (any T <= 3)
+    bool one_wave;
     bool operator<(const TuneKey& o) const {
-        return std::tie(W, H, K, dt, minorant, max_pass) < std::tie(o.W, o.H, o.K, o.dt, o.minorant, o.max_pass);
+        return std::tie(W, H, K, dt, minorant, max_pass, scan_T, one_wave) <
+               std::tie(o.W, o.H, o.K, o.dt, o.minorant, o.max_pass, o.scan_T, o.one_wave);
     }
 };
 std::mutex g_tune_mu;
@@ -968,11 +970,6 @@ std::map<TuneKey, std::pair<Tile, Tile>> g_tune_cache;
 }  // namespace
 }  // namespace dm
 
-// Picks, for the row and the column family separately, the compiled (lanes, labels per
-// lane) tile with the shortest measured half-step on a synthetic instance of the same
-// shape, and writes the choice into p (tile_lanes/labels_per_lane for rows, the _v fields
-// for columns).  Allocates (and frees) scratch device memory; results are cached per
-// (W, H, K, cost dtype, minorant, max_pass) for the process.
 extern "C" int dm_default_tile(int K, int* tile_lanes, int* labels_per_lane) {
     clear_error();
     DM_REQUIRE(tile_lanes != nullptr && labels_per_lane != nullptr, DM_ERR_NULL, "null output");
@@ -983,15 +980,25 @@ extern "C" int dm_default_tile(int K, int* tile_lanes, int* labels_per_lane) {
     return DM_OK;
 }
 
-extern "C" int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_params* p, void* hip_stream) {
-    clear_error();
+// Picks, for the row and the column family separately, the compiled (lanes, labels per
+// lane) tile with the shortest measured half-step on a synthetic instance of the same
+// shape, and writes the choice into p (tile_lanes/labels_per_lane for rows, the _v fields
+// for columns).  Allocates (and frees) scratch device memory; results are cached for the
+// process.  Scan messages (T > 3): the kernels that a solve launches on the tile, pipelined
+// where launch_sweep takes the pipeline.  Window messages: a pipelined launch has the same
+// kernel whatever the tile, which then only serves what runs one wave per chain (launches
+// beyond pipe_per_cu, recording half-steps, the adjoint): the one-wave kernels are timed, as
+// with one_wave (a plan's queue; keep_checkpoints = 2, whose half-steps record).
+int dm::autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_params* p, bool one_wave, void* hip_stream) {
     DM_REQUIRE(p != nullptr, DM_ERR_NULL, "params is NULL");
     int st = validate_params(s, p);
     if (st != DM_OK) return st;
     DM_REQUIRE(p->minorant != DM_MINORANT_HIERARCHICAL, DM_ERR_UNSUPPORTED,
                "the hierarchical minorant uses no chain tiles");
     DM_REQUIRE(cost_dtype == DM_F32 || cost_dtype == DM_F16, DM_ERR_DTYPE, "unknown cost dtype");
-    const TuneKey key{s.W, s.H, s.K, (int)cost_dtype, p->minorant, p->max_pass};
+    const bool scan = p->trunc_T > 3;
+    one_wave = one_wave || !scan || p->keep_checkpoints == 2;
+    const TuneKey key{s.W, s.H, s.K, (int)cost_dtype, p->minorant, p->max_pass, scan ? p->trunc_T : 0, one_wave};
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         auto it = g_tune_cache.find(key);
@@ -1069,16 +1076,19 @@ extern "C" int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_pa
     cols.inv_n = 1.0f / (float)s.H;
 
     Tile best[2] = {default_tile(s.K), default_tile(s.K)};
+    auto launch = [&](Tile t, const SweepArgs& a) {
+        return one_wave ? launch_tile_sweep(t, a, cost_dtype, stream) : launch_sweep(t, a, cost_dtype, stream);
+    };
     for (int fam = 0; fam < 2; ++fam) {
         const SweepArgs& a = fam == 0 ? rows : cols;
         float best_ms = 1e30f;
         for (const Tile& t : kTiles) {
             if (t.G * t.LPL < s.K) continue;
-            if (launch_tile_sweep(t, a, cost_dtype, stream) != hipSuccess) continue;  // warm-up
+            if (launch(t, a) != hipSuccess) continue;  // warm-up
             float ms_min = 1e30f;
             for (int rep = 0; rep < 3; ++rep) {
                 (void)hipEventRecord(e0, stream);
-                (void)launch_tile_sweep(t, a, cost_dtype, stream);
+                (void)launch(t, a);
                 (void)hipEventRecord(e1, stream);
                 if (hipEventSynchronize(e1) != hipSuccess) break;
                 float ms = 0.0f;
@@ -1106,4 +1116,9 @@ extern "C" int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_pa
     p->tile_lanes_v = best[1].G;
     p->labels_per_lane_v = best[1].LPL;
     return DM_OK;
+}
+
+extern "C" int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_params* p, void* hip_stream) {
+    clear_error();
+    return autotune_tiles(s, cost_dtype, p, false, hip_stream);
 }
