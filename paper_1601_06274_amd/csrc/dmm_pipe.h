@@ -299,9 +299,11 @@ struct PipeChain {
 // vector; else one access per label.
 // Node offsets: a lane's offset in a volume is fixed (its label at node 0; out of range for
 // labels and chains that do not exist), the node's offset is scalar and stays inside the
-// chain.  Nodes beyond the end are loaded at an out-of-range lane offset: no access, as the
-// chain's last nodes are stored by another wave while such a load could be in flight, and
-// the next pass's load of the same line could be given what it brought.
+// chain.  Nodes beyond the end are loaded at an out-of-range lane offset: no traffic for
+// values that are never used.  Lines that the storer writes may be loaded meanwhile for other
+// nodes (the end of a row and the start of the next one); the waves of a workgroup share the
+// CU's L1, and what one has stored another reads after both waited for their accesses
+// (pipe_barrier_global).
 template <int G, int LPL, typename TT, bool VEC, bool HAS_THETA>
 struct PipeLane {
     static constexpr int ES = (int)sizeof(TT);
