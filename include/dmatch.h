@@ -167,7 +167,13 @@ typedef struct {
     int   tile_lanes;       /* row chains: 0 = automatic; else lanes per chain (4..64)  */
     int   labels_per_lane;  /* row chains: 0 = automatic; else with tile_lanes*lpl >= K */
     int   tile_lanes_v;     /* column chains: 0 = same as rows (see dm_autotune_tiles)  */
-    int   labels_per_lane_v;
+    int   labels_per_lane_v;/* With trunc_T <= 3 and trunc_T - 1 <= labels per lane the results
+                               are the same bit for bit on every tile, and half-steps may run on
+                               a tile that the library chooses (pipelines of waves, where those
+                               are faster); the given tile then serves launches of one wave per
+                               chain: large frames, keep_checkpoints 2, the backward.  Otherwise
+                               messages are scans, which round by tile, and the given tile is
+                               the one that runs. */
     int   keep_checkpoints; /* for dm_solve_discrete_backward (the size query includes
                                what is kept):
                                0: nothing kept;
@@ -218,9 +224,11 @@ int dm_default_tile(int K, int* tile_lanes, int* labels_per_lane);
 /* Autotuner: measures every compiled (lanes per chain, labels per lane) tile on one
  * half-step of a synthetic instance of shape s (row and column chains separately) and
  * writes the fastest into p->tile_lanes / labels_per_lane (rows) and tile_lanes_v /
- * labels_per_lane_v (columns).  Allocates and frees scratch device memory (unlike the
- * solver calls); synchronises hip_stream; results are cached for the process per
- * (W, H, K, cost dtype, minorant, max_pass). */
+ * labels_per_lane_v (columns).  With trunc_T > 3 it times the kernels that dm_solve_discrete
+ * launches on each tile; with trunc_T <= 3, where those may be the same for every tile, and
+ * with keep_checkpoints 2 the kernels of one wave per chain.  Allocates and frees scratch
+ * device memory (unlike the solver calls); synchronises hip_stream; results are cached for
+ * the process per (W, H, K, cost dtype, minorant, max_pass, trunc_T above 3, kernels timed). */
 int dm_autotune_tiles(dm_shape s, dm_dtype cost_dtype, dm_discrete_params* p, void* hip_stream);
 
 /* Adjoint of dm_solve_discrete (reverse mode; the paper gives no derivative - this is
@@ -362,13 +370,15 @@ int dm_refine_flow(const void* cost, dm_dtype cost_dtype, const int32_t* labels1
 
 /* ---------------------------------------------------------------------------------
  * Batched form: many instances of uneven size (each with its own W, H, K) solved by
- * one hipGraph launch.  dm_plan_batched picks a chain tile per labels count and chain
- * family (dm_autotune_tiles unless p fixes tile_lanes), builds the work tables and
- * captures: per half-step one persistent work-queue launch per tile class (lane
- * groups of chains pulled from an atomic counter, longest chains first; classes run
- * as parallel graph branches), the final row pass (labels), and - if rp != NULL - the
- * refinement of every instance (one launch per primal-dual iteration over all
- * instances' tiles).  The plan owns device memory (work tables, one message volume
+ * one hipGraph launch.  dm_plan_batched builds the work tables and captures: per half-step
+ * one launch per tile class, longest chains first (classes run as parallel graph branches),
+ * the final row pass (labels), and - if rp != NULL - the refinement of every instance (five
+ * primal-dual iterations per launch over all instances' tiles).  A class is pipelines of
+ * waves, a workgroup per group of chains, where results do not depend on the tile (see
+ * tile_lanes) and the pipelines are faster; otherwise a persistent work queue (lane groups
+ * of chains pulled from an atomic counter) on a chain tile per labels count and chain family:
+ * p's tile_lanes, else the fastest of a measurement as dm_autotune_tiles makes it, for kernels
+ * of one wave per chain.  The plan owns device memory (work tables, one message volume
  * per instance, refinement state) until dm_plan_destroy; the caller owns every
  * instance buffer, which must stay valid and at the same addresses.
  * dm_run_batched replays the graph on hip_stream.  Instances with warm_start = 0 get

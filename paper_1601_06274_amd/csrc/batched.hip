@@ -1,10 +1,11 @@
 // batched.hip - many uneven instances in one hipGraph launch (plan / run / destroy).
 //
-// The plan groups instances by their autotuned chain tile, builds per-launch work tables
-// (lane groups of chains, longest chains first) and captures the whole solve once into a
-// hipGraph: per half-step one persistent work-queue launch per tile class (classes run as
-// parallel graph branches), the final row pass, and optionally the batched refinement
-// (one launch per iteration over all instances' tiles).  dm_run_batched replays it.
+// The plan builds per-launch work tables (groups of chains, longest chains first) and captures
+// the whole solve once into a hipGraph: per half-step one launch per tile class (classes run as
+// parallel graph branches), the final row pass, and optionally the batched refinement (five
+// iterations per launch over all instances' tiles).  A class is a workgroup of the pipelined
+// sweeps per item, where they serve and gain, or a persistent work queue of one-wave workers on
+// the autotuned chain tile.  dm_run_batched replays it.
 // Unlike the single-instance calls, the plan allocates and owns device memory (tables,
 // message scratch, refinement state) until dm_plan_destroy.
 #include <algorithm>

@@ -50,11 +50,13 @@ __device__ __forceinline__ int mfield(uint32_t m, int shift, int bits) { return 
 //
 // A pixel's state, model and weights stay in registers; LDS holds what neighbours read: the
 // edges' p - q (phase A, from the right and lower neighbour), the old u and 2 u+ - u (phase
-// B, from the left and upper one).  What bounds it: FP64 issue of the halo's extra pixels
-// against launches and the latency of an iteration (two barriers).  One pixel per thread
-// (16 waves a block, 4 per SIMD) hides that latency where 6 pixels per thread in 4 waves did
-// not; rows that no output of the remaining iterations depends on are skipped (a wave is
-// two rows).
+// B, from the left and upper one).  What bounds it: vector issue (65 % of a busy CU's cycles at
+// 1242 x 375, counted; a sixth of those instructions are FP64 additions, multiplications and
+// FMAs, the rest the compares and selects of the proxes and addresses), 47 % of it for the
+// halo's pixels, against launches and the latency of an iteration (two barriers).  One pixel
+// per thread (16 waves a block, two blocks a CU) hides that latency where 6 pixels per thread
+// in 4 waves did not; rows that no output of the remaining iterations depends on are skipped
+// (a wave is two rows).
 // mask0: the branch-mask plane of the first iteration (nullptr: no tape), mask_stride the
 // element distance between consecutive iterations' planes.
 template <int TX, int TY, int S, class DataProx>

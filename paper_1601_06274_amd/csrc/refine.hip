@@ -23,8 +23,8 @@
 //                      per (instance, tile) of a batched plan's table.
 // State and arithmetic are FP64 (rfloat); the cost volume and edge weights are read in
 // their storage types and widened.  The working set (about 11 doubles per pixel) stays
-// in L2 / MALL at these sizes, so the iteration is bound by on-chip bandwidth and
-// launch latency, not HBM.
+// in L2 / MALL at these sizes, so the iteration is bound by vector issue and launch latency
+// (pdhg.h), not HBM.
 //
 // Adjoint (reverse mode).  Every map of the iteration is piecewise linear; given the
 // recorded branches, the adjoint of one iteration is a linear stencil reaching one pixel,

@@ -29,7 +29,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 PROBE_KERNEL = "MulFunctor"
 
 
-SOURCES = {"sweep": ["dmm_kernels.h", "dmm_pipe.h", "wave.h", "tiles.h"],
+SOURCES = {"sweep": ["dmm_kernels.h", "dmm_pipe.h", "pipe_rule.h", "wave.h", "tiles.h"],
            "adjoint": ["dmm_kernels.h", "wave.h", "tiles.h", "dmm_adjoint.h"],
            "hier": ["dmm_hier.hip", "dmm_hier.h"]}
 
